@@ -55,6 +55,9 @@ def gate_up_kernel_name(d: dict) -> str:
     T, I, E, k = d["T"], d["I"], d["E"], d["k"]
     if d.get("act8"):
         return "grouped_gemm_w8a8_kernel<gate/up>"
+    if T * k <= (32 if d["wdtype"] == "fp8" else 24) * E:
+        name = "stream" if T * k <= 2 * E else "shared"
+        return f"grouped_gemm_{name}_kernel<gate/up, {d['wdtype']} weights>"
     if d["wdtype"] == "fp8":
         return "grouped_gemm_dma_kernel<gate/up, fp8 weights>"
     if (2 * I) % 256:
@@ -64,7 +67,7 @@ def gate_up_kernel_name(d: dict) -> str:
 
 def kernel_source_sha256() -> str:
     h = hashlib.sha256()
-    for f in ("gemm.hip", "common.h", "internal.h"):
+    for f in ("gemm.hip", "gemm_stream.hip", "gemm_common.h", "common.h", "internal.h"):
         with open(os.path.join(ROOT, "paper_2509_17863_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

@@ -16,7 +16,7 @@ PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 BUILD = PKG / "_build"
 LIB = PKG / "libeaas.so"
-SOURCES = ["route.hip", "gemm.hip", "combine.hip", "segments.hip", "quant.hip", "eaas_api.hip"]
+SOURCES = ["route.hip", "gemm.hip", "gemm_stream.hip", "combine.hip", "segments.hip", "quant.hip", "eaas_api.hip"]
 # scheduler variants of the grouped GEMMs: library name -> EAAS_SCHEDULER
 SCHEDULER_VARIANTS = {"scan_all": 1, "walk_all": 2}
 ARCH = "gfx950"

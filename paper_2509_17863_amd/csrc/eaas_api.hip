@@ -387,6 +387,7 @@ int eaas_expert_forward_segments(const eaas_shape* s, const eaas_segment* segs,
   float* stage = reinterpret_cast<float*>(base + L.stage);
   FfnArgs a{};
   a.T = cap; a.H = s->H; a.I = s->I; a.E = s->E; a.k = s->k;
+  a.capacity = true;
   a.x = x_cat;
   a.perm = rt.perm;
   a.offsets = rt.offsets;
@@ -489,6 +490,7 @@ int eaas_server_step(const eaas_shape* s, const eaas_slot* slots, int n_slots,
     if (e != hipSuccess) return EAAS_ERR_HIP;
     FfnArgs a{};
     a.T = cap; a.H = g.H; a.I = g.I; a.E = g.E; a.k = g.k;
+    a.capacity = true;
     a.x = x_cat;
     a.perm = rt.perm;
     a.offsets = rt.offsets;

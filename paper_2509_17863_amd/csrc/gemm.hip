@@ -52,100 +52,19 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.h"
-#include "internal.h"
+#include "gemm_common.h"
 
 namespace eaas {
 namespace {
 
-#define LDS_AS __attribute__((address_space(3)))
-#define CONST_AS __attribute__((address_space(4)))  // read-only global data, scalar loads
-
-constexpr int kNumXcd = 8;
 constexpr int kGroupM = 4;  // M-tiles per ordering group inside an expert
-
-enum GemmKind { kGateUp = 0, kDownPlainK = 1, kDownBySlotK = 2 };
-
-struct GemmParams {
-  const uint16_t* a;      // gate/up: x [T, lda]; down: h [R, lda]
-  const int32_t* perm;    // [R]
-  int k;                  // slots per token
-  int lda;                // K of this GEMM
-  const uint8_t* b;       // weights [E, N, K] (bf16 or fp8 bytes)
-  const float* b_scale;   // [E, N/128, K/128] (fp8)
-  int N;                  // weight rows per expert
-  int K;                  // reduction length
-  int I;                  // intermediate size (gate/up: up rows start at I)
-  const int32_t* offsets; // [E+1]
-  const int32_t* active;  // [E+1]
-  uint16_t* h;            // gate/up output [R, I]
-  float* y;               // down output [R, N]
-  int R;                  // slots (T*k)
-  int E;                  // resident experts (groups)
-  // server step over several layers: group e is expert e % e_layer of layer
-  // e / e_layer, whose weights come from that layer's record instead of b
-  const eaas_layer_weights* layers;  // nullptr: one weight array (b, b_scale)
-  int e_layer;
-  bool down;              // the records' down-projection members
-  // fp8 activations: A is fp8 (a8, rows of K bytes) with one fp32 scale per
-  // row and 128 channels (a_scale [rows, K/128]); the gate/up epilogue writes
-  // h quantized the same way (hq [R, I], hs [R, I/128])
-  const uint8_t* a8;
-  const float* a_scale;
-  uint8_t* hq;
-  float* hs;
-  // fp8 weights in the tiled layout of tile_weights_fp8 (the ring kernels'
-  // weight stages stored contiguously) instead of [E, N, K] row-major
-  bool tiled;
-};
-
-// Weights of group e ([N, K], bf16 or fp8 bytes of esz each).
-__device__ __forceinline__ const uint8_t* group_weights(const GemmParams& p, int e, int esz) {
-  if (p.layers == nullptr) return p.b + (size_t)e * p.N * p.K * esz;
-  const int L = e / p.e_layer;
-  const eaas_layer_weights& lw = p.layers[L];
-  return static_cast<const uint8_t*>(p.down ? lw.w_down : lw.w_gate_up) +
-         (size_t)(e - L * p.e_layer) * p.N * p.K * esz;
-}
-
-// fp8 block scales of group e ([N/128, K/128]).
-__device__ __forceinline__ const float* group_scales(const GemmParams& p, int e) {
-  const size_t per = (size_t)(p.N / 128) * (p.K / 128);
-  if (p.layers == nullptr) return p.b_scale + (size_t)e * per;
-  const int L = e / p.e_layer;
-  const eaas_layer_weights& lw = p.layers[L];
-  return (p.down ? lw.w_down_scale : lw.w_gate_up_scale) + (size_t)(e - L * p.e_layer) * per;
-}
-
-struct Tile {
-  int e;           // expert
-  int tn;          // weight (N) tile
-  int r0;          // first permuted row of the tile
-  int rows_valid;  // rows of the tile that belong to the expert
-};
-
-// silu(g) * u with the hardware exp and reciprocal (a few ulp from the
-// correctly rounded value, which moves rare h roundings by one bf16 ulp).
-__device__ __forceinline__ float silu_mul(float g, float u) {
-  return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
-}
-
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // One wave-wide 16-byte-per-lane DMA from global memory into LDS: lane l
 // reads 16 bytes at base + voff(l) and they land at LDS byte address
 // lds + 16*l.  Issued from inline assembly so the compiler adds no waits of
 // its own; completion is tracked with explicit vmcnt waits.  `base` and `lds`
 // are wave-uniform (SGPRs; `lds` goes to M0).
-// The base is passed through readfirstlane so it is held in SGPRs even where
-// the compiler cannot prove it uniform (free when it already is).
-__device__ __forceinline__ const void* wave_uniform(const void* p) {
-  const uint64_t v = reinterpret_cast<uintptr_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo);
-}
-
+// The base is passed through wave_uniform so it is held in SGPRs.
 // NT sets the nontemporal cache policy: used for weight stages that no other
 // tile of the launch reads (see stream_weights_once), so they do not displace
 // the reused token rows in L2 and the MALL.
@@ -170,22 +89,6 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t 
 #ifndef EAAS_SCHEDULER
 #define EAAS_SCHEDULER 0
 #endif
-
-// Workgroups are dispatched in id order and round-robin over the XCDs
-// (XCD = id mod 8).  The k-th workgroup of XCD x takes tile
-//   (k / 32) * 256 + x * 32 + k % 32,
-// so the 32 workgroups an XCD runs at once hold 32 consecutive tiles (they
-// share token and weight tiles in its L2) and the 256 running on the whole
-// GPU hold one window of 256 consecutive tiles, which keeps the weights the
-// XCDs re-read within the window in the shared MALL.  Tiles past the last
-// whole window keep their ids.
-__device__ __forceinline__ int xcd_window_remap(int bid, int total) {
-  constexpr int kChunk = 32;
-  constexpr int window = kNumXcd * kChunk;
-  if (bid >= (total / window) * window) return bid;
-  const int x = bid % kNumXcd, kk = bid / kNumXcd;
-  return (kk / kChunk) * window + x * kChunk + (kk % kChunk);
-}
 
 // Tile `local` of expert e (0 <= local < its M tiles x n_tiles_n).  Inside an
 // expert, tiles go in groups of kGroupM M-tiles: N-tile major, M-tile minor
@@ -486,15 +389,6 @@ struct DmaSrc {
   uint32_t lds;              // LDS byte address of stage 0
   int wave;
 };
-
-// 8 fp8-e4m3 values -> 8 bf16 (exact).
-__device__ __forceinline__ bf16x8 fp8x8_to_bf16(u32x2 q) {
-  bf16x2 v0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(q[0], 1.0f, false);
-  bf16x2 v1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(q[0], 1.0f, true);
-  bf16x2 v2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(q[1], 1.0f, false);
-  bf16x2 v3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(q[1], 1.0f, true);
-  return bf16x8{v0[0], v0[1], v1[0], v1[1], v2[0], v2[1], v3[0], v3[1]};
-}
 
 template <int KIND, int BK, int SA, int SB, int BSPAN, int NW, int BM, int BN, int MBW, int NBW,
           bool FULL, bool FP8>
@@ -1762,7 +1656,9 @@ __global__ __launch_bounds__(256) void tile_weights_fp8_kernel(const uint8_t* __
   }
 }
 
-// Tile shapes (N a multiple of 256 takes the LDS-DMA kernels):
+// Tile shapes (decode-sized batches of a few rows per expert: the streaming
+// kernels of gemm_stream.hip, see few_rows; else N a multiple of 256 takes the
+// LDS-DMA kernels):
 //   bf16: 256x256 tiles, 8 waves of 128x64 in ping-pong, BK=64;
 //   fp8 weights, gate/up: 96x512 tiles (a decode batch's ~50-90 rows per
 //     expert fit one tile, so the weights stream once), 8 waves of 96x64 --
@@ -1775,8 +1671,10 @@ __global__ __launch_bounds__(256) void tile_weights_fp8_kernel(const uint8_t* __
 //   fp8 weights and activations: 192x256 (prefill) or 128x256 (decode);
 //   N not a multiple of 256: register-staged 128-row tiles.
 template <int KIND, bool FP8>
-hipError_t launch_kind(const GemmParams& p, int R, int E, bool small_m, hipStream_t stream) {
+hipError_t launch_kind(const GemmParams& p, int R, int E, bool small_m, bool few,
+                       hipStream_t stream) {
   const bool n256 = (p.N % 256) == 0;
+  if (few) return launch_gemm_stream<KIND, FP8>(p, R, E, stream);
   if constexpr (FP8) {
     // the down projection runs two 4-wave workgroups of 96x256 per CU: twice
     // the tiles of the 512-wide layout (a shorter tail), and two independent
@@ -1818,6 +1716,22 @@ bool small_rows(const FfnArgs& a) {
   return (long long)a.T * a.k <= 128LL * a.E;
 }
 
+// Batches that the streaming kernels of gemm_stream.hip take: few rows per
+// expert on average, so that most row blocks fit their 64 rows.  Step times,
+// tiled kernels -> streaming (us), by rows per expert:
+//   bf16: qwen3 shape 2: 226 -> 190, 32: 284 -> 261, 48: 298 -> 289, 64: 312 ->
+//         370; with Zipf 1.1 routing 16: 185 -> 187, 32: 230 -> 252
+//         dsv3 shape 16: 503 -> 466, 32: 519 -> 500, 48: 529 -> 530
+//         mixtral shape 2: 571 -> 444, 32: 626 -> 517
+//   fp8:  dsv3 shape 8: 264 -> 233, 32: 278 -> 268, 48: 293 -> 304; with Zipf
+//         1.2 routing 32: 375 -> 330
+//         mixtral shape 8: 411 -> 259, 48: 469 -> 358
+// A dynamic batch passes its capacity, which it rarely fills.
+bool few_rows(const FfnArgs& a) {
+  const long long per_expert = a.capacity ? 48 : a.fp8 ? 32 : 24;
+  return (long long)a.T * a.k <= per_expert * a.E;
+}
+
 }  // namespace
 
 hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N, int K, int I,
@@ -1849,8 +1763,8 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
     g.hs = a.hs;
     return launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
   }
-  return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, small_rows(a), stream)
-               : launch_kind<kGateUp, false>(g, R, a.E, small_rows(a), stream);
+  return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, small_rows(a), few_rows(a), stream)
+               : launch_kind<kGateUp, false>(g, R, a.E, small_rows(a), few_rows(a), stream);
 }
 
 hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
@@ -1871,12 +1785,12 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
     return a.epilogue == kDownBySlot ? launch_w8a8<kDownBySlotK>(g, R, a.E, small_rows(a), stream)
                                      : launch_w8a8<kDownPlainK>(g, R, a.E, small_rows(a), stream);
   }
-  const bool sm = small_rows(a);
+  const bool sm = small_rows(a), few = few_rows(a);
   if (a.epilogue == kDownBySlot)
-    return a.fp8 ? launch_kind<kDownBySlotK, true>(g, R, a.E, sm, stream)
-                 : launch_kind<kDownBySlotK, false>(g, R, a.E, sm, stream);
-  return a.fp8 ? launch_kind<kDownPlainK, true>(g, R, a.E, sm, stream)
-               : launch_kind<kDownPlainK, false>(g, R, a.E, sm, stream);
+    return a.fp8 ? launch_kind<kDownBySlotK, true>(g, R, a.E, sm, few, stream)
+                 : launch_kind<kDownBySlotK, false>(g, R, a.E, sm, few, stream);
+  return a.fp8 ? launch_kind<kDownPlainK, true>(g, R, a.E, sm, few, stream)
+               : launch_kind<kDownPlainK, false>(g, R, a.E, sm, few, stream);
 }
 
 }  // namespace eaas

@@ -1,0 +1,622 @@
+// Grouped expert GEMMs for batches that give an expert a few rows (decode):
+// every wave streams its own weight rows straight into registers.
+//
+// Such a launch is bound by the weight stream from HBM (each weight byte is
+// used for a handful of rows), so what counts is how many bytes the whole
+// chip keeps in flight.  The LDS-tiled kernels of gemm.hip need 256 or 512
+// weight rows per workgroup and a whole CU per workgroup: with few active
+// experts most CUs hold nothing, and with many the start and the end of every
+// tile leave its CU idle.  Here a wave owns 32 weight rows (gate/up: 16 gate
+// rows and the matching 16 up rows) and a ring of D K tiles in registers, so
+// 16 KiB or more are in flight per wave and eight waves share a CU:
+//
+//   grouped_gemm_stream_kernel  one wave per workgroup, token rows loaded like
+//                               the weights; no LDS, no barrier (a row or two
+//                               per expert: latency is everything)
+//   grouped_gemm_shared_kernel  four waves share the token rows of a row block
+//                               through LDS, a chunk of channels at a time
+//                               (loading them per wave costs L2 traffic that
+//                               slows the weights: 16 rows of 7 168 channels
+//                               a quarter)
+//
+// Both operands reach v_mfma_f32_16x16x32_bf16 in its own layout (lane l: row
+// l%16, 8 channels at 8*(l/16) of a 32-channel k-step; src0 = weight rows,
+// src1 = token rows).  That instruction's sums are those of two 32x32x16 steps
+// in ascending k, bit for bit, and the K tiles are walked in ascending order
+// by one wave, so a token's result is the one the tiled kernels give (fp8
+// weights: likewise per 128-channel scale block).
+//
+// Measured (one MI355X, HIP kernel times, tiled kernel -> this file; dsv3: H
+// 7168, I 2048, E 32, k 8; qwen3: H 2048, I 768, E 128, k 8):
+//   dsv3, 1 token, fp8 tiled      gate/up 121 -> 40 us, down 30 -> 22 us
+//   dsv3, 32 tokens, fp8 tiled    gate/up 167 -> 145, down 97 -> 84
+//   dsv3, 64 tokens, bf16         gate/up 289 -> 295, down 225 -> 189
+//   qwen3, 16 tokens, bf16        gate/up 130 -> 102, down 60 -> 49
+//   qwen3, 192 tokens, bf16       gate/up 180 -> 153, down 85 -> 83
+#include <algorithm>
+
+#include "gemm_common.h"
+
+namespace eaas {
+namespace {
+
+// Non-temporal: a weight byte is read once in the launch, and without the hint
+// the stream runs 5% slower (dsv3, 1 token: 78 against 74 us per step).
+__device__ __forceinline__ u32x4 load_weights(const uint8_t* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+}
+
+// Exchanges a bit of the register index (lo, hi) with bit 3 of the lane
+// index: lo keeps its lanes with bit 3 clear and takes hi's in the others'
+// place, hi the other way round.
+__device__ __forceinline__ void swap_reg_lane3(uint32_t& lo, uint32_t& hi) {
+  constexpr int kRor8 = 0x128;  // rotate by 8 inside a row of 16 lanes
+  const uint32_t a = lo, b = hi;
+  lo = __builtin_amdgcn_update_dpp(a, b, kRor8, 0xf, 0xc, false);
+  hi = __builtin_amdgcn_update_dpp(b, a, kRor8, 0xf, 0x3, false);
+}
+// The same with bit 4 of the lane index.
+__device__ __forceinline__ void swap_reg_lane4(uint32_t& lo, uint32_t& hi) {
+  const auto r = __builtin_amdgcn_permlane16_swap(lo, hi, false, false);
+  lo = r[0];
+  hi = r[1];
+}
+
+// Weight layouts: bf16 rows, fp8 rows, fp8 tiled.
+enum StreamWeights { kBf16Rows = 0, kFp8Rows = 1, kFp8Tiled = 2 };
+
+// A K tile is 128 bytes of each weight row.  MFMA wants lane l to hold row
+// l%16 and 16-byte chunks l/16, l/16 + 4 (bf16) or 8-byte pieces l/16,
+// l/16 + 4, ... (fp8) of those 128 bytes, but a load in that order asks memory for 64
+// or 32 bytes of 16 rows at a time.  So each load takes whole 128-byte lines
+// (8 rows; tiled fp8: 16 rows of 64 contiguous bytes, 1 KiB in all), and the
+// chunks are put in place by swapping register-index bits with lane-index
+// bits just before the MFMAs.
+constexpr int kBlocks = 2;  // 16-row weight blocks of a wave
+
+template <int W, int MB, int D>
+struct StreamLoop {
+  static constexpr bool FP8 = W != kBf16Rows, kTiled = W == kFp8Tiled;
+  static constexpr int KT = FP8 ? 128 : 64;  // channels per K tile
+  static constexpr int KS = KT / 32;         // MFMA k-steps per K tile
+
+  struct Weights {
+    const uint8_t* w;        // the expert's (wave-uniform)
+    uint32_t step;           // bytes to the next K tile
+    uint32_t second;         // bytes from the first to the second load of a block
+    uint32_t off[kBlocks];   // per lane
+    const CONST_AS float* sc[kBlocks];  // fp8: scales of the block's rows
+  };
+  struct Rows {
+    const uint8_t* x;        // wave-uniform
+    uint32_t off[MB];        // per lane
+  };
+  struct Stage {
+    u32x4 w[kBlocks][2];
+    float sc[kBlocks];
+    bf16x8 x[MB][KS];        // not used where the rows come through LDS
+  };
+
+  // Byte offset inside the K tile and row that lane l loads for block row 0.
+  static __device__ __forceinline__ int lane_row(int lane) {
+    return W == kFp8Tiled ? lane & 15 : lane & 7;
+  }
+  static __device__ __forceinline__ int lane_byte(int lane) {
+    const int b3 = (lane >> 3) & 1, b4 = (lane >> 4) & 1, b5 = lane >> 5;
+    if (W == kFp8Tiled) return 16 * (2 * b4 + b5);          // lane bits 5,4 = piece bits 1,2
+    if (W == kFp8Rows) return 16 * (4 * b4 + 2 * b3 + b5);  // bits 5,4,3 = piece bits 1,3,2
+    return 16 * (4 * b3 + 2 * b5 + b4);                     // bits 5,4,3 = chunk bits 1,0,2
+  }
+
+  static __device__ __forceinline__ void load_w(const Weights& s, int kt, Stage& f) {
+    const uint8_t* wk = s.w + (size_t)kt * s.step;
+#pragma unroll
+    for (int j = 0; j < kBlocks; ++j) {
+      f.w[j][0] = load_weights(wk + s.off[j]);
+      f.w[j][1] = load_weights(wk + s.second + s.off[j]);
+    }
+    if (FP8) {
+#pragma unroll
+      for (int j = 0; j < kBlocks; ++j) f.sc[j] = s.sc[j][kt];
+    }
+  }
+  static __device__ __forceinline__ void load_x(const Rows& x, int kt, Stage& f) {
+    const uint8_t* xk = x.x + (size_t)kt * (KT * 2);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        f.x[i][ks] = *reinterpret_cast<const bf16x8*>(xk + ks * 64 + x.off[i]);
+  }
+
+  // The block's weight fragment of each k-step.
+  static __device__ __forceinline__ void fragments(const u32x4 (&w)[2], bf16x8 (&f)[KS]) {
+    u32x4 a = w[0], b = w[1];
+    if constexpr (W == kBf16Rows) {
+      // register = row bit 3, lane bits 5,4,3 = chunk bits 1,0,2
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t lo = a[i], hi = b[i];
+        swap_reg_lane3(lo, hi);
+        a[i] = lo;
+        b[i] = hi;
+      }
+      f[0] = __builtin_bit_cast(bf16x8, a);
+      f[1] = __builtin_bit_cast(bf16x8, b);
+    } else {
+      // piece bit 0 = which 8-byte half of a load
+      uint32_t v[2][2][2];  // [load][half][word]
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        v[0][0][c] = a[c];
+        v[0][1][c] = a[2 + c];
+        v[1][0][c] = b[c];
+        v[1][1][c] = b[2 + c];
+        swap_reg_lane4(v[0][0][c], v[0][1][c]);
+        swap_reg_lane4(v[1][0][c], v[1][1][c]);
+        if (W == kFp8Rows) {
+          swap_reg_lane3(v[0][0][c], v[1][0][c]);
+          swap_reg_lane3(v[0][1][c], v[1][1][c]);
+        }
+      }
+      // rows: the load index now is piece bit 2 and the half piece bit 3;
+      // tiled: the load index is piece bit 3 and the half piece bit 2
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int ld = W == kFp8Rows ? ks & 1 : ks >> 1, half = W == kFp8Rows ? ks >> 1 : ks & 1;
+        f[ks] = fp8x8_to_bf16(u32x2{v[ld][half][0], v[ld][half][1]});
+      }
+    }
+  }
+
+  static __device__ __forceinline__ void multiply(const Stage& f, f32x4 (&acc)[MB][kBlocks]) {
+    if constexpr (FP8) {
+#pragma unroll
+      for (int j = 0; j < kBlocks; ++j) {
+        bf16x8 w[KS];
+        fragments(f.w[j], w);
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          f32x4 part = {};
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks)
+            part = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks], f.x[i][ks], part, 0, 0, 0);
+          acc[i][j] += f.sc[j] * part;
+        }
+      }
+    } else {
+      bf16x8 w[kBlocks][KS];
+#pragma unroll
+      for (int j = 0; j < kBlocks; ++j) fragments(f.w[j], w[j]);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < kBlocks; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j][ks], f.x[i][ks], acc[i][j],
+                                                                0, 0, 0);
+    }
+  }
+
+  // The scheduling barriers keep the compiler from sinking a load to its use
+  // D tiles later.  Loads that the loop skips near the end come after it: a
+  // skipped load inside would make the compiler's wait counts assume the worst.
+  static __device__ __forceinline__ void start(const Weights& s, int nk, Stage (&st)[D]) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) load_w(s, min(d, nk - 1), st[d]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  static __device__ __forceinline__ void run(const Weights& s, const Rows& x, int nk,
+                                             Stage (&st)[D], f32x4 (&acc)[MB][kBlocks]) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) load_x(x, min(d, nk - 1), st[d]);
+    __builtin_amdgcn_sched_barrier(0);
+    int k0 = 0;
+    for (; k0 + 2 * D <= nk; k0 += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        multiply(st[d], acc);
+        load_w(s, k0 + d + D, st[d]);
+        load_x(x, k0 + d + D, st[d]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (k0 + d < nk) multiply(st[d], acc);
+      if (k0 + d + D < nk) {
+        load_w(s, k0 + d + D, st[d]);
+        load_x(x, k0 + d + D, st[d]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+      if (k0 + d + D < nk) multiply(st[d], acc);
+  }
+};
+
+// Weight source of wave `wt` of expert e: output columns from c0 on.
+template <int KIND, class Loop>
+__device__ __forceinline__ typename Loop::Weights weight_source(const GemmParams& p, int e,
+                                                                int c0) {
+  constexpr bool GATEUP = KIND == kGateUp;
+  constexpr int ESZ = Loop::FP8 ? 1 : 2;
+  const int lane = __lane_id();
+  typename Loop::Weights s;
+  s.w = static_cast<const uint8_t*>(wave_uniform(group_weights(p, e, ESZ)));
+  // tiled: stages of bn rows x 64 bytes, stored one after the other along K
+  const int bn = GATEUP && p.N % 512 == 0 ? 512 : 256;
+  s.step = Loop::kTiled ? bn * 128 : 128;
+  s.second = Loop::kTiled ? bn * 64 : 8u * (uint32_t)(p.K * ESZ);
+#pragma unroll
+  for (int j = 0; j < kBlocks; ++j) {
+    const int row = GATEUP ? j * p.I + c0 : c0 + j * 16;  // first weight row of the block
+    if (Loop::kTiled) {
+      const int tn = GATEUP ? c0 / (bn / 2) : c0 / bn;
+      const int jr = GATEUP ? c0 % (bn / 2) + j * (bn / 2) : c0 % bn + j * 16;
+      s.off[j] = (uint32_t)tn * (uint32_t)(p.K / 64) * (bn * 64) +
+                 (jr + Loop::lane_row(lane)) * 64 + Loop::lane_byte(lane);
+    } else {
+      s.off[j] =
+          (uint32_t)(row + Loop::lane_row(lane)) * (uint32_t)(p.K * ESZ) + Loop::lane_byte(lane);
+    }
+    s.sc[j] = Loop::FP8 ? (const CONST_AS float*)wave_uniform(
+                              group_scales(p, e) + (size_t)(row / 128) * (p.K / 128))
+                        : nullptr;
+  }
+  return s;
+}
+
+// Permuted rows r0 + m (m clamped into [0, rows)): the row of the A operand,
+// and the row of the output.
+template <int KIND>
+__device__ __forceinline__ int source_row(const GemmParams& p, int r) {
+  return KIND == kGateUp ? min(max(p.perm[r], 0), p.R - 1) / p.k : r;
+}
+template <int KIND>
+__device__ __forceinline__ int output_row(const GemmParams& p, int r) {
+  return KIND == kDownBySlotK ? min(max(p.perm[r], 0), p.R - 1) : r;
+}
+
+// acc[i][j][v]: token row 16i + lane%16 of the block's `rows`, weight row
+// 4*(lane/16) + v of block j.
+template <int KIND, int MB>
+__device__ __forceinline__ void store_rows(const GemmParams& p, int rows, int c0,
+                                           const int (&orow)[MB],
+                                           const f32x4 (&acc)[MB][kBlocks]) {
+  const int lane = __lane_id();
+  const int l16 = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    if (i * 16 + l16 >= rows) continue;
+    if constexpr (KIND == kGateUp) {
+      const f32x4 g = acc[i][0], u = acc[i][1];
+      u32x2 v;
+      v[0] = pack_bf16x2(silu_mul(g[0], u[0]), silu_mul(g[1], u[1]));
+      v[1] = pack_bf16x2(silu_mul(g[2], u[2]), silu_mul(g[3], u[3]));
+      *reinterpret_cast<u32x2*>(p.h + (size_t)orow[i] * p.I + c0 + 4 * q) = v;
+    } else {
+#pragma unroll
+      for (int j = 0; j < kBlocks; ++j)
+        *reinterpret_cast<f32x4*>(p.y + (size_t)orow[i] * p.N + c0 + j * 16 + 4 * q) = acc[i][j];
+    }
+  }
+}
+
+// Rows [r0, r0 + rows) of expert e (rows <= 16*MB) times this wave's weights.
+template <int KIND, int W, int MB, int D>
+__device__ __forceinline__ void stream_tile(const GemmParams& p, int e, int r0, int rows, int wt) {
+  using Loop = StreamLoop<W, MB, D>;
+  const int lane = __lane_id();
+  const int l16 = lane & 15, q = lane >> 4;
+  const int c0 = wt * (KIND == kGateUp ? 16 : 32);
+  const typename Loop::Weights s = weight_source<KIND, Loop>(p, e, c0);
+  const int nk = p.K / Loop::KT;
+  typename Loop::Stage st[D];
+  Loop::start(s, nk, st);
+  typename Loop::Rows x;
+  x.x = reinterpret_cast<const uint8_t*>(p.a);
+  int orow[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int m = i * 16 + l16;
+    const int r = r0 + (m < rows ? m : 0);
+    orow[i] = output_row<KIND>(p, r);
+    x.off[i] = (uint32_t)source_row<KIND>(p, r) * (uint32_t)(p.lda * 2) + q * 16;
+  }
+  f32x4 acc[MB][kBlocks];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < kBlocks; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  Loop::run(s, x, nk, st, acc);
+  store_rows<KIND, MB>(p, rows, c0, orow, acc);
+}
+
+// grid: min(E, R) * N / 32 waves, one per workgroup: wave wt of the a-th active
+// expert, whose rows it takes 32 at a time.  (A ring of 8 K tiles with 16 rows,
+// 5 with 32: 4 and 3 were within 3%; past 256 registers fewer waves would fit.)
+template <int KIND, int W>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void grouped_gemm_stream_kernel(GemmParams p) {
+  constexpr bool FP8 = W != kBf16Rows;
+  const int waves_n = p.N / 32;
+  const int a = blockIdx.x / waves_n;
+  const int wt = blockIdx.x - a * waves_n;
+  // routing arrays may come from the caller: clamp every index taken from them
+  if (a >= min(max(p.active[0], 0), p.E)) return;
+  const int e = min(max(p.active[1 + a], 0), p.E - 1);
+  const int r0 = min(max(p.offsets[e], 0), p.R);
+  const int end = min(max(p.offsets[e + 1], r0), p.R);
+  for (int r = r0; r < end; r += 32) {
+    if (end - r <= 16) stream_tile<KIND, W, 1, FP8 ? 5 : 8>(p, e, r, end - r, wt);
+    else stream_tile<KIND, W, 2, FP8 ? 3 : 5>(p, e, r, min(32, end - r), wt);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same streams with the token rows shared through LDS: a row block's
+// channels are staged in chunks of CHB bytes per row, double-buffered, one
+// barrier per chunk.  The next chunk's loads are issued a whole chunk before
+// they are stored to LDS; since loads return in order, that wait leaves the
+// weight tiles issued since (TPC per wave) in flight.
+template <int W, int MB, int NW, int CHB, int D>
+struct SharedLoop {
+  using S = StreamLoop<W, 1, D>;  // weight loads and fragments
+  static constexpr bool FP8 = S::FP8;
+  static constexpr int KT = S::KT, KS = S::KS;
+  static constexpr int TPC = CHB / (KT * 2);  // K tiles per chunk of token rows
+  static_assert(TPC >= 1 && D % TPC == 0, "ring slots are compile-time indexes");
+  static constexpr int LPR = CHB / 16;        // lanes per row when staging
+  static constexpr int RP = NW * kWave / LPR; // rows per staging pass
+  static_assert(MB * 16 % RP == 0, "whole staging passes");
+  static constexpr int NP = MB * 16 / RP;
+  static constexpr int XROW = CHB + 16;       // 16-byte pad: a fragment read hits every bank once
+
+  struct Rows {
+    const uint8_t* x;    // wave-uniform
+    uint32_t off[NP];    // per thread: byte offset of its row of each pass
+    uint32_t kbyte, kmax;  // this thread's 16 bytes inside a chunk; last 16 bytes of a row
+    LDS_AS char* dst;    // this thread's place in pass 0 of buffer 0
+    uint32_t buf;        // bytes of one buffer
+    u32x4 r[NP];         // the chunk on its way
+  };
+  static __device__ __forceinline__ void load_x(Rows& x, int c) {
+    const uint32_t kb = min((uint32_t)(c * CHB) + x.kbyte, x.kmax);
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      x.r[p] = *reinterpret_cast<const u32x4*>(x.x + (size_t)(x.off[p] + kb));
+  }
+  static __device__ __forceinline__ void store_x(const Rows& x, int c) {
+    LDS_AS char* d = x.dst + (c & 1) * x.buf;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      *reinterpret_cast<LDS_AS u32x4*>(d + p * RP * XROW) = x.r[p];
+  }
+
+  static __device__ __forceinline__ void multiply(const typename S::Stage& f,
+                                                  const LDS_AS char* xs,
+                                                  f32x4 (&acc)[MB][kBlocks]) {
+    bf16x8 w[kBlocks][KS];
+    f32x4 part[FP8 ? MB : 1][FP8 ? kBlocks : 1];
+#pragma unroll
+    for (int j = 0; j < kBlocks; ++j) S::fragments(f.w[j], w[j]);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      bf16x8 x[MB];
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        x[i] = *reinterpret_cast<const LDS_AS bf16x8*>(xs + i * 16 * XROW + ks * 64);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < kBlocks; ++j) {
+          if constexpr (FP8)
+            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                w[j][ks], x[i], ks == 0 ? f32x4{} : part[i][j], 0, 0, 0);
+          else
+            acc[i][j] =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j][ks], x[i], acc[i][j], 0, 0, 0);
+        }
+    }
+    if constexpr (FP8) {
+#pragma unroll
+      for (int j = 0; j < kBlocks; ++j)
+#pragma unroll
+        for (int i = 0; i < MB; ++i) acc[i][j] += f.sc[j] * part[i][j];
+    }
+  }
+
+  // Chunk c has been read: the next one goes into the other buffer, which
+  // every wave finished reading before the last barrier.
+  static __device__ __forceinline__ void next_chunk(Rows& x, int c, int nch) {
+    store_x(x, c + 1);
+    load_x(x, min(c + 2, nch - 1));
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  }
+
+  static __device__ __forceinline__ void run(const typename S::Weights& s, Rows& x, int nk,
+                                             typename S::Stage (&st)[D], const LDS_AS char* xs,
+                                             f32x4 (&acc)[MB][kBlocks]) {
+    const int nch = (nk + TPC - 1) / TPC;
+    load_x(x, 0);
+    store_x(x, 0);
+    load_x(x, min(1, nch - 1));
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    int k0 = 0;
+    for (; k0 + 2 * D <= nk; k0 += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int c = (k0 + d) / TPC;
+        multiply(st[d], xs + (c & 1) * x.buf + (d % TPC) * (KT * 2), acc);
+        S::load_w(s, k0 + d + D, st[d]);
+        if ((d + 1) % TPC == 0) next_chunk(x, c, nch);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < 2 * D - 1; ++d) {
+      const int kt = k0 + d, c = kt / TPC;
+      if (kt < nk) multiply(st[d % D], xs + (c & 1) * x.buf + (d % TPC) * (KT * 2), acc);
+      if (d < D && kt + D < nk) S::load_w(s, kt + D, st[d % D]);
+      if ((d + 1) % TPC == 0 && c + 1 < nch) next_chunk(x, c, nch);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+};
+
+template <int KIND, int W, int MB, int NW, int CHB, int D>
+__device__ __forceinline__ void shared_tile(const GemmParams& p, int e, int r0, int rows, int wt,
+                                            LDS_AS char* lds) {
+  using Loop = SharedLoop<W, MB, NW, CHB, D>;
+  using S = typename Loop::S;
+  const int lane = __lane_id();
+  const int l16 = lane & 15, q = lane >> 4;
+  const int c0 = wt * (KIND == kGateUp ? 16 : 32);
+  const typename S::Weights s = weight_source<KIND, S>(p, e, c0);
+  const int nk = p.K / Loop::KT;
+  typename S::Stage st[D];
+  S::start(s, nk, st);
+  typename Loop::Rows x;
+  x.x = reinterpret_cast<const uint8_t*>(p.a);
+  x.kbyte = (threadIdx.x % Loop::LPR) * 16;
+  x.kmax = (uint32_t)p.K * 2 - 16;
+  x.buf = MB * 16 * Loop::XROW;
+  x.dst = lds + (threadIdx.x / Loop::LPR) * Loop::XROW + x.kbyte;
+#pragma unroll
+  for (int i = 0; i < Loop::NP; ++i) {
+    const int m = threadIdx.x / Loop::LPR + i * Loop::RP;
+    x.off[i] =
+        (uint32_t)source_row<KIND>(p, r0 + (m < rows ? m : 0)) * (uint32_t)(p.lda * 2);
+  }
+  int orow[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int m = i * 16 + l16;
+    orow[i] = output_row<KIND>(p, r0 + (m < rows ? m : 0));
+  }
+  f32x4 acc[MB][kBlocks];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < kBlocks; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  Loop::run(s, x, nk, st, lds + l16 * Loop::XROW + q * 16, acc);
+  store_rows<KIND, MB>(p, rows, c0, orow, acc);
+}
+
+// Row block of a workgroup: the experts' rows in blocks of at most BM rows
+// (an expert's blocks are of equal height, rounded up to 16 rows), expert
+// major, then weight tile major and row block minor.  Every wave finds its
+// block by itself: 64 experts at a time, one per lane.
+struct RowBlock {
+  int e, r0, rows, tn;
+};
+template <int BM>
+__device__ __forceinline__ bool locate_rows(const GemmParams& p, int tile, int tiles_n,
+                                            RowBlock& b) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int n_active = min(max(p.active[0], 0), p.E);
+  int before = 0;
+  for (int a0 = 0; a0 < n_active; a0 += kWave) {
+    // routing arrays may come from the caller: clamp every index taken from them
+    const int a = a0 + lane;
+    int e = 0, beg = 0, rows = 0;
+    if (a < n_active) {
+      e = min(max(p.active[1 + a], 0), p.E - 1);
+      beg = min(max(p.offsets[e], 0), p.R);
+      rows = min(max(p.offsets[e + 1], beg), p.R) - beg;
+    }
+    const int blocks = (rows + BM - 1) / BM;
+    int incl = blocks;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int o = __shfl_up(incl, d, kWave);
+      if (lane >= d) incl += o;
+    }
+    const int end = (before + incl) * tiles_n;
+    const uint64_t past = ballot(tile < end);
+    if (past) {
+      const int l = __builtin_ctzll(past);
+      const int first = before + __builtin_amdgcn_readlane(incl - blocks, l);
+      const int nb = __builtin_amdgcn_readlane(blocks, l);
+      const int local = tile - first * tiles_n;
+      b.e = __builtin_amdgcn_readlane(e, l);
+      const int all = __builtin_amdgcn_readlane(rows, l);
+      const int height = ((all + nb - 1) / nb + 15) & ~15;
+      b.tn = local / nb;
+      const int m0 = (local - b.tn * nb) * height;
+      b.r0 = __builtin_amdgcn_readlane(beg, l) + m0;
+      b.rows = min(height, all - m0);
+      return b.rows > 0;
+    }
+    before += __builtin_amdgcn_readlane(incl, kWave - 1);
+  }
+  return false;
+}
+
+// Four waves (128 weight rows), blocks of up to 64 rows, 512-byte chunks and a
+// ring of 4 K tiles: two workgroups per CU by registers and LDS (67.6 KB).
+// (Blocks of 32 rows with three or four workgroups per CU were within 4% up
+// to 24 rows per expert and read the weights twice past 32; 256-byte chunks
+// were 3-15% slower.)
+constexpr int kSharedWaves = 4, kSharedRows = 64, kSharedChunk = 512, kSharedRing = 4;
+
+// grid: row blocks x N / 128.
+template <int KIND, int W>
+__global__ __launch_bounds__(kWave * kSharedWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void grouped_gemm_shared_kernel(GemmParams p) {
+  constexpr int NW = kSharedWaves, CHB = kSharedChunk, D = kSharedRing;
+  __shared__ __attribute__((aligned(16))) char smem[2 * kSharedRows * (CHB + 16)];
+  RowBlock b;
+  const int tile = xcd_window_remap(blockIdx.x, gridDim.x);
+  if (!locate_rows<kSharedRows>(p, tile, p.N / (32 * NW), b)) return;
+  const int wt = b.tn * NW + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  LDS_AS char* lds = (LDS_AS char*)smem;
+  if (b.rows <= 16) shared_tile<KIND, W, 1, NW, CHB, D>(p, b.e, b.r0, b.rows, wt, lds);
+  else if (b.rows <= 32) shared_tile<KIND, W, 2, NW, CHB, D>(p, b.e, b.r0, b.rows, wt, lds);
+  else if (b.rows <= 48) shared_tile<KIND, W, 3, NW, CHB, D>(p, b.e, b.r0, b.rows, wt, lds);
+  else shared_tile<KIND, W, 4, NW, CHB, D>(p, b.e, b.r0, b.rows, wt, lds);
+}
+
+template <int KIND, int W>
+hipError_t enqueue(const GemmParams& p, int R, int E, hipStream_t stream) {
+  // one wave per workgroup up to two rows per expert on average: with the
+  // waves of 1 to 16 tokens its start-up is shorter (qwen3, 1 token: gate/up
+  // 25 -> 16 us, 16 tokens 108 -> 102); from 2 rows on they are equal, and
+  // past 4 the rows that every wave loads by itself cost more
+  const bool alone = (long long)R <= 2LL * E;
+  const long long grid =
+      alone ? (long long)std::min(E, R) * (p.N / 32)
+            : ((long long)(R + kSharedRows - 1) / kSharedRows + std::min(E, R)) *
+                  (p.N / (32 * kSharedWaves));
+  if (grid <= 0) return hipSuccess;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (alone)
+    hipLaunchKernelGGL((grouped_gemm_stream_kernel<KIND, W>), dim3((unsigned)grid), dim3(kWave), 0,
+                       stream, p);
+  else
+    hipLaunchKernelGGL((grouped_gemm_shared_kernel<KIND, W>), dim3((unsigned)grid),
+                       dim3(kWave * kSharedWaves), 0, stream, p);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+template <int KIND, bool FP8>
+hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, hipStream_t stream) {
+  if constexpr (!FP8) return enqueue<KIND, kBf16Rows>(p, R, E, stream);
+  else if (p.tiled) return enqueue<KIND, kFp8Tiled>(p, R, E, stream);
+  else return enqueue<KIND, kFp8Rows>(p, R, E, stream);
+}
+
+template hipError_t launch_gemm_stream<kGateUp, false>(const GemmParams&, int, int, hipStream_t);
+template hipError_t launch_gemm_stream<kGateUp, true>(const GemmParams&, int, int, hipStream_t);
+template hipError_t launch_gemm_stream<kDownPlainK, false>(const GemmParams&, int, int, hipStream_t);
+template hipError_t launch_gemm_stream<kDownPlainK, true>(const GemmParams&, int, int, hipStream_t);
+template hipError_t launch_gemm_stream<kDownBySlotK, false>(const GemmParams&, int, int, hipStream_t);
+template hipError_t launch_gemm_stream<kDownBySlotK, true>(const GemmParams&, int, int, hipStream_t);
+
+}  // namespace eaas

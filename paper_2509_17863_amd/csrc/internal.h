@@ -55,6 +55,8 @@ struct FfnArgs {
   float* hs = nullptr;          // [R,I/128]
   // fp8 weights stored in the tiled layout of launch_tile_weights_fp8
   bool tiled = false;
+  // T is the capacity of a dynamic batch: the batch itself is usually smaller
+  bool capacity = false;
 };
 
 // x [rows,K] bf16 -> q [rows,K] e4m3fn and s [rows,K/128]: per row and 128

@@ -1,0 +1,76 @@
+"""The streaming GEMM kernels of decode-sized batches (a few rows per expert):
+row counts at the edges of their 16-row blocks and 64-row tiles, more than 64
+active experts, and K of one tile, an odd number of 128-channel blocks and
+several ring lengths.
+
+Against the oracle, and bit for bit against the same tokens inside a batch
+large enough for the tiled kernels (a token's result does not depend on the
+batch around it).
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import eaas_oracle as O
+from paper_2509_17863_amd import eaas, synth
+from paper_2509_17863_amd.device_io import to_device
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+# rows per expert; the rest of the E experts stay empty.  "alone" has at most
+# two rows per expert on average (one wave per workgroup), "shared" more.
+EDGES = {
+    "alone": (128, [33, 17, 16, 15, 2] + [1] * 68),
+    "shared": (100, [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 97, 130, 0, 2] + [3] * 60),
+    "one expert": (1, [20]),
+}
+
+
+def run(dev, k, wdt):
+    T, H = dev["x"].shape
+    E, twoI, _ = dev["w_gate_up"].shape
+    I = twoI // 2
+    ws = eaas.alloc_workspace(T, H, I, E, k, wdt)
+    ws.fill_(0xFF)
+    out = torch.full((T, H), float("nan"), dtype=torch.float32, device="cuda")
+    eaas.eaas_expert_forward(dev["x"], dev["topk_ids"], dev["topk_weights"], dev["w_gate_up"],
+                             dev["w_down"], out, ws, dev["w_gate_up_scale"], dev["w_down_scale"],
+                             tiled=wdt == eaas.EAAS_FP8_E4M3_TILED)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("rows", list(EDGES))
+@pytest.mark.parametrize("wdtype", ["bf16", "fp8", "tiled"])
+@pytest.mark.parametrize("H,I", [(128, 128), (384, 256), (1280, 640), (2048, 128)])
+def test_row_counts_and_k_lengths(gpu, rows, wdtype, H, I):
+    if wdtype == "tiled" and H % 256:
+        pytest.skip("the tiled layout needs H a multiple of 256")
+    E, counts = EDGES[rows]
+    print(f"few rows: {rows} {wdtype} H={H} I={I} E={E} R={sum(counts)}", flush=True)
+    rng = np.random.default_rng(len(counts) + H + I)
+    small = rng.permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)
+    big = np.concatenate([small, rng.integers(0, E, 49 * E + 200).astype(np.int32)])
+    d = synth.make_inputs(len(big), H, I, E, 1, 77, wdtype="bf16" if wdtype == "bf16" else "fp8")
+    d["topk_ids"] = big[:, None].copy()
+    d["topk_weights"] = rng.uniform(0.2, 1.0, (len(big), 1)).astype(np.float32)
+    sub = O.sub_batch(d, np.arange(len(small)))
+    wdt = {"bf16": eaas.EAAS_BF16, "fp8": eaas.EAAS_FP8_E4M3,
+           "tiled": eaas.EAAS_FP8_E4M3_TILED}[wdtype]
+
+    def device(inp):
+        dev = to_device(inp)
+        if wdtype == "tiled":
+            for key, which in (("w_gate_up", eaas.EAAS_GATE_UP), ("w_down", eaas.EAAS_DOWN)):
+                t = torch.empty_like(dev[key])
+                eaas.eaas_tile_weights_fp8(dev[key], which, H, I, t)
+                dev[key] = t
+        return dev
+
+    got = run(device(sub), 1, wdt)
+    whole = run(device(d), 1, wdt)
+    assert np.array_equal(got.view(np.uint32), whole[: len(small)].view(np.uint32))
+    ref = O.expert_forward(sub)["out"]
+    rms = float(np.sqrt((ref ** 2).mean()))
+    assert float(np.abs(got - ref).max()) <= TOL * rms
