@@ -55,13 +55,13 @@ def gate_up_kernel_name(d: dict) -> str:
     T, I, E, k = d["T"], d["I"], d["E"], d["k"]
     if d.get("act8"):
         return "grouped_gemm_w8a8_kernel<gate/up>"
-    if T * k <= (32 if d["wdtype"] == "fp8" else 24) * E:
-        name = "stream" if T * k <= 2 * E else "shared"
-        return f"grouped_gemm_{name}_kernel<gate/up, {d['wdtype']} weights>"
-    if d["wdtype"] == "fp8":
+    fp8, R = d["wdtype"] == "fp8", T * k
+    if R <= (32 if fp8 else 24) * E:
+        return f"grouped_gemm_{'stream' if R <= 2 * E else 'shared'}_kernel<gate/up, {d['wdtype']}>"
+    if R <= 120 * E and (fp8 or E * (2 * I // 128) <= 256):
+        return f"grouped_gemm_shared_kernel<gate/up, {d['wdtype']}, 144 rows>"
+    if fp8:
         return "grouped_gemm_dma_kernel<gate/up, fp8 weights>"
-    if (2 * I) % 256:
-        return "grouped_gemm_kernel<gate/up, register-staged>"
     return "grouped_gemm_pp_kernel<gate/up>"
 
 

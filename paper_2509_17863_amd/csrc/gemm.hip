@@ -35,8 +35,8 @@
 // The fp8-weight down projection runs two 4-wave workgroups per CU.  The
 // down epilogues stage each wave's accumulators through LDS so the fp32
 // rows go out as whole 256-byte row segments.
-// A register-staged loop covers shapes the DMA tiles do not (N not a multiple
-// of 256).
+// Batches of a few rows per expert take the streaming kernels of
+// gemm_stream.hip instead (stream_shape below).
 // LDS rows are BK elements long; 16-byte chunk c of row r is stored at chunk
 // c ^ swz(r) so 32-row fragment reads hit every bank once.
 //
@@ -765,183 +765,6 @@ void grouped_gemm_dma_kernel(GemmParams p) {
   }
 }
 
-// ============================================================================
-// fp8 weights (and generic shapes): register-staged double buffer, BK = 64
-// ============================================================================
-constexpr int kBK = 64;
-
-// 16 fp8-e4m3 values -> 16 bf16 (exact), as two 16-byte chunks.
-__device__ __forceinline__ void fp8x16_to_bf16(const u32x4 q, u32x4& lo, u32x4& hi) {
-  uint32_t o[8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    bf16x2 a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(q[i], 1.0f, false);
-    bf16x2 b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(q[i], 1.0f, true);
-    o[2 * i] = __builtin_bit_cast(uint32_t, a);
-    o[2 * i + 1] = __builtin_bit_cast(uint32_t, b);
-  }
-  lo = u32x4{o[0], o[1], o[2], o[3]};
-  hi = u32x4{o[4], o[5], o[6], o[7]};
-}
-
-template <int KIND, bool FP8, int WM, int WN, int MBW, int NBW>
-__global__ __launch_bounds__(WM * WN * kWave) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void grouped_gemm_kernel(GemmParams p) {
-  constexpr int NT = WM * WN * kWave;  // threads
-  constexpr int BM = WM * MBW * 32;
-  constexpr int BN = WN * NBW * 32;
-  constexpr bool GATEUP = KIND == kGateUp;
-  static_assert(!GATEUP || (NBW % 2 == 0), "gate/up pairs gate and up blocks");
-  constexpr int ROWS_PER_PASS = NT / 8;  // rows covered by one 16-byte load per thread
-  constexpr int A_LOADS = BM / ROWS_PER_PASS;
-  constexpr int B_ROWS_PER_PASS = FP8 ? NT / 4 : NT / 8;
-  constexpr int B_LOADS = BN / B_ROWS_PER_PASS;
-  static_assert(BM % ROWS_PER_PASS == 0 && BN % B_ROWS_PER_PASS == 0, "tile/thread shape");
-
-  __shared__ bf16x8 As[2][BM * 8];
-  __shared__ bf16x8 Bs[2][BN * 8];
-  __shared__ int s_tp[kMaxExperts + 1];
-  __shared__ int s_exp[kMaxExperts];
-  __shared__ int s_wave[NT / kWave + 1];
-
-  Tile t;
-  if (!locate_tile<BM, BN, NT>(p, s_tp, s_exp, s_wave, t)) return;
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
-  const int e = t.e, tn = t.tn, r0 = t.r0, rows_valid = t.rows_valid;
-
-  // A: thread loads chunk (tid % 8) of rows tid/8 + i*ROWS_PER_PASS
-  const int a_chunk = tid & 7;
-  int a_off[A_LOADS];
-#pragma unroll
-  for (int i = 0; i < A_LOADS; ++i) {
-    const int rr = tid / 8 + i * ROWS_PER_PASS;
-    const int r = r0 + (rr < rows_valid ? rr : 0);
-    const int src_row = GATEUP ? min(max(p.perm[r], 0), p.R - 1) / p.k : r;
-    a_off[i] = src_row * p.lda + a_chunk * 8;
-  }
-  const size_t esz = FP8 ? 1 : 2;
-  const uint8_t* bexp = group_weights(p, e, (int)esz);
-  constexpr int B_CHUNKS = FP8 ? 4 : 8;  // 16-byte chunks per 64-wide K slice
-  const int b_chunk = tid % B_CHUNKS;
-  int b_off[B_LOADS];
-#pragma unroll
-  for (int i = 0; i < B_LOADS; ++i) {
-    const int j = tid / B_CHUNKS + i * B_ROWS_PER_PASS;
-    const int wrow = weight_row<GATEUP, BN>(p, tn, j);
-    b_off[i] = (wrow * p.K + b_chunk * 16 / (int)esz) * (int)esz;  // bytes
-  }
-
-  u32x4 ra[A_LOADS];
-  u32x4 rb[B_LOADS];
-  auto load_global = [&](int kt) {
-    const int k0 = kt * kBK;
-#pragma unroll
-    for (int i = 0; i < A_LOADS; ++i)
-      ra[i] = *reinterpret_cast<const u32x4*>(p.a + a_off[i] + k0);
-#pragma unroll
-    for (int i = 0; i < B_LOADS; ++i)
-      rb[i] = *reinterpret_cast<const u32x4*>(bexp + b_off[i] + (size_t)k0 * esz);
-  };
-  auto store_lds = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) {
-      const int rr = tid / 8 + i * ROWS_PER_PASS;
-      As[buf][rr * 8 + (a_chunk ^ (rr & 7))] = __builtin_bit_cast(bf16x8, ra[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < B_LOADS; ++i) {
-      const int j = tid / B_CHUNKS + i * B_ROWS_PER_PASS;
-      if (FP8) {
-        u32x4 lo, hi;
-        fp8x16_to_bf16(rb[i], lo, hi);
-        Bs[buf][j * 8 + ((2 * b_chunk) ^ (j & 7))] = __builtin_bit_cast(bf16x8, lo);
-        Bs[buf][j * 8 + ((2 * b_chunk + 1) ^ (j & 7))] = __builtin_bit_cast(bf16x8, hi);
-      } else {
-        Bs[buf][j * 8 + (b_chunk ^ (j & 7))] = __builtin_bit_cast(bf16x8, rb[i]);
-      }
-    }
-  };
-
-  const int wm = wave / WN;
-  const int wn = wave % WN;
-  const int lrow = lane & 31;
-  const int khalf = lane >> 5;
-  const int am0 = wm * MBW * 32;  // first token row of this wave inside the tile
-  int bn0[NBW];
-#pragma unroll
-  for (int j = 0; j < NBW; ++j) bn0[j] = block_row<GATEUP, BN, NBW>(wn, j);
-  const int mb_live =
-      __builtin_amdgcn_readfirstlane(max(0, min(MBW, ceil_div(rows_valid - am0, 32))));
-
-  f32x16 acc[MBW][NBW];
-  f32x16 part[FP8 ? MBW : 1][FP8 ? NBW : 1];
-#pragma unroll
-  for (int i = 0; i < MBW; ++i)
-#pragma unroll
-    for (int j = 0; j < NBW; ++j) acc[i][j] = f32x16{};
-  if (FP8) {
-#pragma unroll
-    for (int i = 0; i < (FP8 ? MBW : 1); ++i)
-#pragma unroll
-      for (int j = 0; j < (FP8 ? NBW : 1); ++j) part[i][j] = f32x16{};
-  }
-
-  const RowInfo<MBW> ri = row_info<KIND, MBW>(p, t, am0, mb_live);
-  const int nk = p.K / kBK;
-  load_global(0);
-  store_lds(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) load_global(kt + 1);
-#pragma unroll
-    for (int kk = 0; kk < kBK / 16; ++kk) {
-      const int chunk = 2 * kk + khalf;
-      bf16x8 bf[NBW];
-#pragma unroll
-      for (int j = 0; j < NBW; ++j) {
-        const int row = bn0[j] + lrow;
-        bf[j] = Bs[cur][row * 8 + (chunk ^ (row & 7))];
-      }
-#pragma unroll
-      for (int i = 0; i < MBW; ++i) {
-        if (i < mb_live) {
-          const int row = am0 + i * 32 + lrow;
-          const bf16x8 af = As[cur][row * 8 + (chunk ^ (row & 7))];
-#pragma unroll
-          for (int j = 0; j < NBW; ++j) {
-            if (FP8)
-              part[FP8 ? i : 0][FP8 ? j : 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                  bf[j], af, part[FP8 ? i : 0][FP8 ? j : 0], 0, 0, 0);
-            else
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[j], af, acc[i][j], 0, 0, 0);
-          }
-        }
-      }
-    }
-    if (FP8 && (kt & 1)) {
-      // end of a 128-wide K block: acc += scale * partial
-      const int kb = kt >> 1;
-      const float* sexp = group_scales(p, e);
-#pragma unroll
-      for (int j = 0; j < NBW; ++j) {
-        const int wrow = weight_row<GATEUP, BN>(p, tn, bn0[j]);
-        const float sc = sexp[(wrow / 128) * (p.K / 128) + kb];
-#pragma unroll
-        for (int i = 0; i < MBW; ++i) {
-          acc[i][j] += sc * part[FP8 ? i : 0][FP8 ? j : 0];
-          part[FP8 ? i : 0][FP8 ? j : 0] = f32x16{};
-        }
-      }
-    }
-    if (kt + 1 < nk) store_lds(cur ^ 1);
-    __syncthreads();
-  }
-  epilogue<KIND, BN, MBW, NBW>(p, t, wn, am0, mb_live, ri, acc);
-}
-
 // worst case M-tiles over any routing of R rows onto at most min(E, R) experts
 inline long long grid_tiles(int R, int E, int BM, int BN, int N) {
   const long long mt = (long long)(R + BM - 1) / BM + (E < R ? E : R);
@@ -957,18 +780,6 @@ inline long long grid_tiles(int R, int E, int BM, int BN, int N) {
 // expert, 1% slower).  Results do not change.
 inline bool stream_weights_once(int R, int E, int BM) {
   return (long long)R <= (long long)BM * E;
-}
-
-template <int KIND, bool FP8, int WM, int WN, int MBW, int NBW>
-hipError_t launch_reg(const GemmParams& p, int R, int E, hipStream_t stream) {
-  constexpr int BM = WM * MBW * 32;
-  constexpr int BN = WN * NBW * 32;
-  const long long grid = grid_tiles(R, E, BM, BN, p.N);
-  if (grid <= 0) return hipSuccess;
-  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((grouped_gemm_kernel<KIND, FP8, WM, WN, MBW, NBW>), dim3((unsigned)grid),
-                     dim3(WM * WN * kWave), 0, stream, p);
-  return hipGetLastError();
 }
 
 template <int KIND, bool FP8, int BK, int SA, int SB, int BSPAN, int WM, int WN, int MBW, int NBW,
@@ -1656,44 +1467,34 @@ __global__ __launch_bounds__(256) void tile_weights_fp8_kernel(const uint8_t* __
   }
 }
 
-// Tile shapes (decode-sized batches of a few rows per expert: the streaming
-// kernels of gemm_stream.hip, see few_rows; else N a multiple of 256 takes the
-// LDS-DMA kernels):
+// Tile shapes of the LDS-DMA kernels:
 //   bf16: 256x256 tiles, 8 waves of 128x64 in ping-pong, BK=64;
-//   fp8 weights, gate/up: 96x512 tiles (a decode batch's ~50-90 rows per
-//     expert fit one tile, so the weights stream once), 8 waves of 96x64 --
-//     two per SIMD, so one wave's partial-sum scaling (VALU) overlaps the
-//     other's MFMAs -- BK=64, 2 token-row stages and 4 weight stages
-//     (152 KiB), so 96 KiB of weights per CU are in flight while a tile is
-//     multiplied (96x256 with 4 waves and 3+3 stages when N is not a
-//     multiple of 512);
-//   fp8 weights, down: 96x256 tiles of 4 waves, two workgroups per CU;
-//   fp8 weights and activations: 192x256 (prefill) or 128x256 (decode);
-//   N not a multiple of 256: register-staged 128-row tiles.
+//   fp8 weights, gate/up: 96x512 tiles, 8 waves of 96x64 -- two per SIMD, so
+//     one wave's partial-sum scaling (VALU) overlaps the other's MFMAs --
+//     BK=64, 2 token-row stages and 4 weight stages (152 KiB), so 96 KiB of
+//     weights per CU are in flight while a tile is multiplied (96x256 with 4
+//     waves and 3+3 stages when N is not a multiple of 512);
+//   fp8 weights, down: 96x256 tiles of 4 waves, two workgroups per CU: twice
+//     the tiles of the 512-wide layout (a shorter tail), and two independent
+//     barrier domains per CU;
+//   fp8 weights and activations: 192x256 (prefill) or 128x256 (decode).
+// They cover N / 256 whole tiles; of an N that is no multiple of 256 the last
+// 128 rows go to the streaming kernel.
 template <int KIND, bool FP8>
-hipError_t launch_kind(const GemmParams& p, int R, int E, bool small_m, bool few,
-                       hipStream_t stream) {
-  const bool n256 = (p.N % 256) == 0;
-  if (few) return launch_gemm_stream<KIND, FP8>(p, R, E, stream);
-  if constexpr (FP8) {
-    // the down projection runs two 4-wave workgroups of 96x256 per CU: twice
-    // the tiles of the 512-wide layout (a shorter tail), and two independent
-    // barrier domains per CU
-    if constexpr (KIND != kGateUp) {
-      if (n256) return launch_dma<KIND, true, 64, 2, 3, 1, 1, 4, 3, 2, 2>(p, R, E, stream);
-    } else {
-      if (p.N % 512 == 0) return launch_dma<KIND, true, 64, 2, 4, 1, 1, 8, 3, 2>(p, R, E, stream);
-      if (n256) return launch_dma<KIND, true, 64, 3, 3, 1, 1, 4, 3, 2>(p, R, E, stream);
-    }
-    if (small_m) return launch_reg<KIND, true, 1, 2, 4, 2>(p, R, E, stream);
-    return launch_reg<KIND, true, 2, 2, 4, 2>(p, R, E, stream);
-  } else {
-    // the ping-pong kernel also beats the register-staged loop on
-    // decode-sized batches (its weight stream keeps more bytes in flight)
-    if (n256) return launch_pp<KIND>(p, R, E, stream);
-    if (small_m) return launch_reg<KIND, false, 1, 2, 4, 2>(p, R, E, stream);
-    return launch_reg<KIND, false, 2, 2, 4, 2>(p, R, E, stream);
-  }
+hipError_t launch_kind(GemmParams p, int R, int E, StreamShape shape, hipStream_t stream) {
+  if (shape != kNotStreamed) return launch_gemm_stream<KIND, FP8>(p, R, E, shape, stream);
+  hipError_t e;
+  if constexpr (!FP8)
+    e = launch_pp<KIND>(p, R, E, stream);
+  else if constexpr (KIND != kGateUp)
+    e = launch_dma<KIND, true, 64, 2, 3, 1, 1, 4, 3, 2, 2>(p, R, E, stream);
+  else if (p.N % 512 == 0)
+    e = launch_dma<KIND, true, 64, 2, 4, 1, 1, 8, 3, 2>(p, R, E, stream);
+  else
+    e = launch_dma<KIND, true, 64, 3, 3, 1, 1, 4, 3, 2>(p, R, E, stream);
+  if (e != hipSuccess || p.N % 256 == 0) return e;
+  p.tn0 = p.N / 256 * 2;
+  return launch_gemm_stream<KIND, FP8>(p, R, E, kStreamWide4, stream);
 }
 
 GemmParams common_params(const FfnArgs& a) {
@@ -1716,9 +1517,11 @@ bool small_rows(const FfnArgs& a) {
   return (long long)a.T * a.k <= 128LL * a.E;
 }
 
-// Batches that the streaming kernels of gemm_stream.hip take: few rows per
-// expert on average, so that most row blocks fit their 64 rows.  Step times,
-// tiled kernels -> streaming (us), by rows per expert:
+// Which batches the streaming kernels of gemm_stream.hip take, by the slots per
+// resident expert.  A dynamic batch passes its capacity, which it rarely fills
+// (and slots of other servers' experts count too), so its limits are higher.
+//
+// Few rows: step times, tiled kernels -> streaming (us), by slots per expert:
 //   bf16: qwen3 shape 2: 226 -> 190, 32: 284 -> 261, 48: 298 -> 289, 64: 312 ->
 //         370; with Zipf 1.1 routing 16: 185 -> 187, 32: 230 -> 252
 //         dsv3 shape 16: 503 -> 466, 32: 519 -> 500, 48: 529 -> 530
@@ -1726,10 +1529,27 @@ bool small_rows(const FfnArgs& a) {
 //   fp8:  dsv3 shape 8: 264 -> 233, 32: 278 -> 268, 48: 293 -> 304; with Zipf
 //         1.2 routing 32: 375 -> 330
 //         mixtral shape 8: 411 -> 259, 48: 469 -> 358
-// A dynamic batch passes its capacity, which it rarely fills.
-bool few_rows(const FfnArgs& a) {
-  const long long per_expert = a.capacity ? 48 : a.fp8 ? 32 : 24;
-  return (long long)a.T * a.k <= per_expert * a.E;
+// One 144-row block per expert (up to 120 slots, so that random counts stay
+// below 144): the fp8 gate/up GEMM, whose tiled kernel needs a second tile past
+// 96 rows: dsv3 shape 64 slots 209 -> 182 us, 64 with Zipf 1.2 302 -> 264, 96:
+// 327 -> 239; at 128 it is 336 -> 355.  (The down GEMM's smaller tiled
+// workgroups are as fast: 64: 132 -> 129, 96: 163 -> 159.)
+// The same where 128-row tiles at most fill the chip once, so that the tiled
+// kernels' 256-row ones leave half of it idle: down GEMM, mixtral shape, bf16
+// 64 slots 281 -> 185 us, 128: 288 -> 222, fp8 111: 227 -> 187; a bf16 gate/up
+// of 8 experts x 1 024 rows, 64 slots: 33 -> 27.
+// N no multiple of 256: the streaming kernel alone up to 350 slots per expert
+// or two rounds of its blocks (whole step, H 1920, I 640, E 24, k 6: 200 slots
+// 103 against 101 us with the tiled kernel for N / 256 tiles and the streaming
+// one for the rest, 300: 137 against 131, 500: 201 against 214; H 384, I 128,
+// E 5, k 2, 280 slots: 43 against 32).
+StreamShape stream_shape(const FfnArgs& a, bool gateup) {
+  const long long R = (long long)a.T * a.k, N = gateup ? 2LL * a.I : a.H;
+  if (R <= (a.capacity ? 48 : a.fp8 ? 32 : 24) * (long long)a.E) return kStreamFew;
+  if (N % 256 && (R <= 350LL * a.E || (R / 144 + a.E) * (N / 128) <= 512)) return kStreamWide4;
+  if (R > (a.capacity ? 480 : 120) * (long long)a.E) return kNotStreamed;
+  if (a.E * (N / 128) <= 256) return kStreamWide4;
+  return a.fp8 && gateup ? kStreamWide8 : kNotStreamed;
 }
 
 }  // namespace
@@ -1763,8 +1583,9 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
     g.hs = a.hs;
     return launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
   }
-  return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, small_rows(a), few_rows(a), stream)
-               : launch_kind<kGateUp, false>(g, R, a.E, small_rows(a), few_rows(a), stream);
+  const StreamShape shape = stream_shape(a, true);
+  return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, shape, stream)
+               : launch_kind<kGateUp, false>(g, R, a.E, shape, stream);
 }
 
 hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
@@ -1785,12 +1606,12 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
     return a.epilogue == kDownBySlot ? launch_w8a8<kDownBySlotK>(g, R, a.E, small_rows(a), stream)
                                      : launch_w8a8<kDownPlainK>(g, R, a.E, small_rows(a), stream);
   }
-  const bool sm = small_rows(a), few = few_rows(a);
+  const StreamShape shape = stream_shape(a, false);
   if (a.epilogue == kDownBySlot)
-    return a.fp8 ? launch_kind<kDownBySlotK, true>(g, R, a.E, sm, few, stream)
-                 : launch_kind<kDownBySlotK, false>(g, R, a.E, sm, few, stream);
-  return a.fp8 ? launch_kind<kDownPlainK, true>(g, R, a.E, sm, few, stream)
-               : launch_kind<kDownPlainK, false>(g, R, a.E, sm, few, stream);
+    return a.fp8 ? launch_kind<kDownBySlotK, true>(g, R, a.E, shape, stream)
+                 : launch_kind<kDownBySlotK, false>(g, R, a.E, shape, stream);
+  return a.fp8 ? launch_kind<kDownPlainK, true>(g, R, a.E, shape, stream)
+               : launch_kind<kDownPlainK, false>(g, R, a.E, shape, stream);
 }
 
 }  // namespace eaas

@@ -10,6 +10,7 @@ namespace eaas {
 
 #define LDS_AS __attribute__((address_space(3)))
 #define CONST_AS __attribute__((address_space(4)))  // read-only global data, scalar loads
+#define GLOBAL_AS __attribute__((address_space(1)))
 
 enum GemmKind { kGateUp = 0, kDownPlainK = 1, kDownBySlotK = 2 };
 
@@ -44,6 +45,7 @@ struct GemmParams {
   // fp8 weights in the tiled layout of tile_weights_fp8 (the ring kernels'
   // weight stages stored contiguously) instead of [E, N, K] row-major
   bool tiled;
+  int tn0;                // streaming kernels: first N tile of the launch
 };
 
 // Weights of group e ([N, K], bf16 or fp8 bytes of esz each).
@@ -115,8 +117,12 @@ __device__ __forceinline__ const void* wave_uniform(const void* p) {
   return reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo);
 }
 
-// The register-streaming kernel (gemm_stream.hip).
+// The register-streaming kernels (gemm_stream.hip): row blocks of up to 64 rows
+// (one wave or four per workgroup), or of up to 144 rows by 256 or 128 weight
+// rows.
+enum StreamShape { kNotStreamed = 0, kStreamFew = 1, kStreamWide8 = 2, kStreamWide4 = 3 };
 template <int KIND, bool FP8>
-hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, hipStream_t stream);
+hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, StreamShape shape,
+                              hipStream_t stream);
 
 }  // namespace eaas

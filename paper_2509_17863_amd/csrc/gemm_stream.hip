@@ -13,11 +13,11 @@
 //   grouped_gemm_stream_kernel  one wave per workgroup, token rows loaded like
 //                               the weights; no LDS, no barrier (a row or two
 //                               per expert: latency is everything)
-//   grouped_gemm_shared_kernel  four waves share the token rows of a row block
-//                               through LDS, a chunk of channels at a time
-//                               (loading them per wave costs L2 traffic that
-//                               slows the weights: 16 rows of 7 168 channels
-//                               a quarter)
+//   grouped_gemm_shared_kernel  four or eight waves share the token rows of a
+//                               row block through LDS, a chunk of channels at
+//                               a time (loading them per wave costs L2 traffic
+//                               that slows the weights: 16 rows of 7 168
+//                               channels a quarter)
 //
 // Both operands reach v_mfma_f32_16x16x32_bf16 in its own layout (lane l: row
 // l%16, 8 channels at 8*(l/16) of a 32-channel k-step; src0 = weight rows,
@@ -27,12 +27,15 @@
 // weights: likewise per 128-channel scale block).
 //
 // Measured (one MI355X, HIP kernel times, tiled kernel -> this file; dsv3: H
-// 7168, I 2048, E 32, k 8; qwen3: H 2048, I 768, E 128, k 8):
-//   dsv3, 1 token, fp8 tiled      gate/up 121 -> 40 us, down 30 -> 22 us
-//   dsv3, 32 tokens, fp8 tiled    gate/up 167 -> 145, down 97 -> 84
-//   dsv3, 64 tokens, bf16         gate/up 289 -> 295, down 225 -> 189
-//   qwen3, 16 tokens, bf16        gate/up 130 -> 102, down 60 -> 49
-//   qwen3, 192 tokens, bf16       gate/up 180 -> 153, down 85 -> 83
+// 7168, I 2048, E 32, k 8; qwen3: H 2048, I 768, E 128, k 8; mixtral: H 4096,
+// I 14336, E 8, k 2):
+//   dsv3, 1 token, fp8 tiled      gate/up 121 -> 39 us, down 30 -> 22 us
+//   dsv3, 32 tokens, fp8 tiled    gate/up 169 -> 146, down 97 -> 81
+//   dsv3, 64 tokens, bf16         gate/up 288 -> 285, down 226 -> 187
+//   qwen3, 16 tokens, bf16        gate/up 129 -> 107, down 60 -> 45
+//   qwen3, 192 tokens, bf16       gate/up 181 -> 152, down 86 -> 81
+//   dsv3, 256 tokens, fp8 tiled   gate/up 209 -> 182 (wide8; 5.2 TB/s)
+//   mixtral, 445 tokens, fp8      gate/up 394 -> 306 (wide8), down 227 -> 187 (wide4)
 #include <algorithm>
 
 #include "gemm_common.h"
@@ -42,8 +45,10 @@ namespace {
 
 // Non-temporal: a weight byte is read once in the launch, and without the hint
 // the stream runs 5% slower (dsv3, 1 token: 78 against 74 us per step).
-__device__ __forceinline__ u32x4 load_weights(const uint8_t* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+// (The pointer says that it is global memory: a flat load would count against
+// the LDS reads' waits too and drain the ring at every fragment read.)
+__device__ __forceinline__ u32x4 load_weights(const GLOBAL_AS uint8_t* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const GLOBAL_AS u32x4*>(p));
 }
 
 // Exchanges a bit of the register index (lo, hi) with bit 3 of the lane
@@ -81,7 +86,7 @@ struct StreamLoop {
   static constexpr int KS = KT / 32;         // MFMA k-steps per K tile
 
   struct Weights {
-    const uint8_t* w;        // the expert's (wave-uniform)
+    const GLOBAL_AS uint8_t* w;  // the expert's (wave-uniform)
     uint32_t step;           // bytes to the next K tile
     uint32_t second;         // bytes from the first to the second load of a block
     uint32_t off[kBlocks];   // per lane
@@ -109,7 +114,7 @@ struct StreamLoop {
   }
 
   static __device__ __forceinline__ void load_w(const Weights& s, int kt, Stage& f) {
-    const uint8_t* wk = s.w + (size_t)kt * s.step;
+    const GLOBAL_AS uint8_t* wk = s.w + (size_t)kt * s.step;
 #pragma unroll
     for (int j = 0; j < kBlocks; ++j) {
       f.w[j][0] = load_weights(wk + s.off[j]);
@@ -245,7 +250,7 @@ __device__ __forceinline__ typename Loop::Weights weight_source(const GemmParams
   constexpr int ESZ = Loop::FP8 ? 1 : 2;
   const int lane = __lane_id();
   typename Loop::Weights s;
-  s.w = static_cast<const uint8_t*>(wave_uniform(group_weights(p, e, ESZ)));
+  s.w = (const GLOBAL_AS uint8_t*)wave_uniform(group_weights(p, e, ESZ));
   // tiled: stages of bn rows x 64 bytes, stored one after the other along K
   const int bn = GATEUP && p.N % 512 == 0 ? 512 : 256;
   s.step = Loop::kTiled ? bn * 128 : 128;
@@ -400,32 +405,27 @@ struct SharedLoop {
                                                   const LDS_AS char* xs,
                                                   f32x4 (&acc)[MB][kBlocks]) {
     bf16x8 w[kBlocks][KS];
-    f32x4 part[FP8 ? MB : 1][FP8 ? kBlocks : 1];
 #pragma unroll
     for (int j = 0; j < kBlocks; ++j) S::fragments(f.w[j], w[j]);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      bf16x8 x[MB];
+    for (int i = 0; i < MB; ++i) {
+      bf16x8 x[KS];
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
-        x[i] = *reinterpret_cast<const LDS_AS bf16x8*>(xs + i * 16 * XROW + ks * 64);
+      for (int ks = 0; ks < KS; ++ks)
+        x[ks] = *reinterpret_cast<const LDS_AS bf16x8*>(xs + i * 16 * XROW + ks * 64);
+      f32x4 part[kBlocks];
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+      for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
         for (int j = 0; j < kBlocks; ++j) {
-          if constexpr (FP8)
-            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                w[j][ks], x[i], ks == 0 ? f32x4{} : part[i][j], 0, 0, 0);
-          else
-            acc[i][j] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j][ks], x[i], acc[i][j], 0, 0, 0);
+          f32x4& to = FP8 ? part[j] : acc[i][j];
+          to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j][ks], x[ks],
+                                                       FP8 && ks == 0 ? f32x4{} : to, 0, 0, 0);
         }
-    }
-    if constexpr (FP8) {
+      if (FP8) {
 #pragma unroll
-      for (int j = 0; j < kBlocks; ++j)
-#pragma unroll
-        for (int i = 0; i < MB; ++i) acc[i][j] += f.sc[j] * part[i][j];
+        for (int j = 0; j < kBlocks; ++j) acc[i][j] += f.sc[j] * part[j];
+      }
     }
   }
 
@@ -557,66 +557,108 @@ __device__ __forceinline__ bool locate_rows(const GemmParams& p, int tile, int t
   return false;
 }
 
-// Four waves (128 weight rows), blocks of up to 64 rows, 512-byte chunks and a
-// ring of 4 K tiles: two workgroups per CU by registers and LDS (67.6 KB).
-// (Blocks of 32 rows with three or four workgroups per CU were within 4% up
-// to 24 rows per expert and read the weights twice past 32; 256-byte chunks
-// were 3-15% slower.)
-constexpr int kSharedWaves = 4, kSharedRows = 64, kSharedChunk = 512, kSharedRing = 4;
+// Geometry of a launch: NW waves (32 weight rows each), row blocks of up to
+// 16*MBX rows, a ring of D K tiles per wave, OCC waves per SIMD.  512-byte
+// chunks of token rows (256-byte ones, with twice the barriers, were 3-25%
+// slower).
+//   few    four waves, 64 rows, two workgroups per CU.  (32 rows with three or
+//          four per CU were within 4% up to 24 rows per expert and read the
+//          weights twice past 32.)
+//   wide8  eight waves, 144 rows (what two chunks of LDS hold), one workgroup
+//          per CU: one block for the 50 to 130 rows that a decode batch of some
+//          hundred tokens gives an expert, in steps of 16 rows, where the
+//          tiled fp8 kernel steps by 32 and needs two tiles past 96.  A ring
+//          of 2: 4 leave too few registers to read fragments ahead (+6%).
+//   wide4  the same with four waves: twice the workgroups, for matrices that
+//          have too few 256-row tiles for the chip.
+template <int W>
+struct Few {
+  static constexpr int NW = 4, MBX = 4, D = 4, OCC = 2;
+};
+template <int W>
+struct Wide8 {
+  static constexpr int NW = 8, MBX = 9, D = W == kBf16Rows ? 4 : 2, OCC = 2;
+};
+template <int W>
+struct Wide4 {
+  static constexpr int NW = 4, MBX = 9, D = W == kBf16Rows ? 4 : 2, OCC = 1;
+};
+constexpr int kChunk = 512;
 
-// grid: row blocks x N / 128.
-template <int KIND, int W>
-__global__ __launch_bounds__(kWave * kSharedWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// The smallest of shared_tile's row counts that holds the block.
+template <int KIND, int W, class G, int MB>
+__device__ __forceinline__ void tile_of_height(const GemmParams& p, const RowBlock& b, int wt,
+                                               LDS_AS char* lds) {
+  if (MB == 1 || b.rows > 16 * (MB - 1))
+    shared_tile<KIND, W, MB, G::NW, kChunk, G::D>(p, b.e, b.r0, b.rows, wt, lds);
+  else if constexpr (MB > 1)
+    tile_of_height<KIND, W, G, MB - 1>(p, b, wt, lds);
+}
+
+// grid: row blocks x N tiles of 32 * NW weight rows, from tile tn0 on.
+template <int KIND, int W, class G>
+__global__ __launch_bounds__(kWave * G::NW) __attribute__((amdgpu_waves_per_eu(G::OCC, G::OCC)))
 void grouped_gemm_shared_kernel(GemmParams p) {
-  constexpr int NW = kSharedWaves, CHB = kSharedChunk, D = kSharedRing;
-  __shared__ __attribute__((aligned(16))) char smem[2 * kSharedRows * (CHB + 16)];
+  constexpr int ROWS = 16 * G::MBX;
+  __shared__ __attribute__((aligned(16))) char smem[2 * ROWS * (kChunk + 16)];
   RowBlock b;
   const int tile = xcd_window_remap(blockIdx.x, gridDim.x);
-  if (!locate_rows<kSharedRows>(p, tile, p.N / (32 * NW), b)) return;
-  const int wt = b.tn * NW + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  LDS_AS char* lds = (LDS_AS char*)smem;
-  if (b.rows <= 16) shared_tile<KIND, W, 1, NW, CHB, D>(p, b.e, b.r0, b.rows, wt, lds);
-  else if (b.rows <= 32) shared_tile<KIND, W, 2, NW, CHB, D>(p, b.e, b.r0, b.rows, wt, lds);
-  else if (b.rows <= 48) shared_tile<KIND, W, 3, NW, CHB, D>(p, b.e, b.r0, b.rows, wt, lds);
-  else shared_tile<KIND, W, 4, NW, CHB, D>(p, b.e, b.r0, b.rows, wt, lds);
+  if (!locate_rows<ROWS>(p, tile, p.N / (32 * G::NW) - p.tn0, b)) return;
+  const int wt = (p.tn0 + b.tn) * G::NW + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  tile_of_height<KIND, W, G, G::MBX>(p, b, wt, (LDS_AS char*)smem);
+}
+
+template <int KIND, int W, class G>
+hipError_t launch_shared(const GemmParams& p, int R, int E, hipStream_t stream) {
+  constexpr int ROWS = 16 * G::MBX;
+  if (p.N % (32 * G::NW)) return hipErrorInvalidValue;
+  const long long grid =
+      ((long long)(R + ROWS - 1) / ROWS + std::min(E, R)) * (p.N / (32 * G::NW) - p.tn0);
+  if (grid <= 0) return hipSuccess;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((grouped_gemm_shared_kernel<KIND, W, G>), dim3((unsigned)grid),
+                     dim3(kWave * G::NW), 0, stream, p);
+  return hipGetLastError();
 }
 
 template <int KIND, int W>
-hipError_t enqueue(const GemmParams& p, int R, int E, hipStream_t stream) {
+hipError_t enqueue(const GemmParams& p, int R, int E, StreamShape shape, hipStream_t stream) {
+  if (shape == kStreamWide8) return launch_shared<KIND, W, Wide8<W>>(p, R, E, stream);
+  if (shape == kStreamWide4) return launch_shared<KIND, W, Wide4<W>>(p, R, E, stream);
   // one wave per workgroup up to two rows per expert on average: with the
   // waves of 1 to 16 tokens its start-up is shorter (qwen3, 1 token: gate/up
   // 25 -> 16 us, 16 tokens 108 -> 102); from 2 rows on they are equal, and
   // past 4 the rows that every wave loads by itself cost more
-  const bool alone = (long long)R <= 2LL * E;
-  const long long grid =
-      alone ? (long long)std::min(E, R) * (p.N / 32)
-            : ((long long)(R + kSharedRows - 1) / kSharedRows + std::min(E, R)) *
-                  (p.N / (32 * kSharedWaves));
+  if ((long long)R > 2LL * E) return launch_shared<KIND, W, Few<W>>(p, R, E, stream);
+  const long long grid = (long long)std::min(E, R) * (p.N / 32);
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (alone)
-    hipLaunchKernelGGL((grouped_gemm_stream_kernel<KIND, W>), dim3((unsigned)grid), dim3(kWave), 0,
-                       stream, p);
-  else
-    hipLaunchKernelGGL((grouped_gemm_shared_kernel<KIND, W>), dim3((unsigned)grid),
-                       dim3(kWave * kSharedWaves), 0, stream, p);
+  hipLaunchKernelGGL((grouped_gemm_stream_kernel<KIND, W>), dim3((unsigned)grid), dim3(kWave), 0,
+                     stream, p);
   return hipGetLastError();
 }
 
 }  // namespace
 
 template <int KIND, bool FP8>
-hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, hipStream_t stream) {
-  if constexpr (!FP8) return enqueue<KIND, kBf16Rows>(p, R, E, stream);
-  else if (p.tiled) return enqueue<KIND, kFp8Tiled>(p, R, E, stream);
-  else return enqueue<KIND, kFp8Rows>(p, R, E, stream);
+hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, StreamShape shape,
+                              hipStream_t stream) {
+  if constexpr (!FP8) return enqueue<KIND, kBf16Rows>(p, R, E, shape, stream);
+  else if (p.tiled) return enqueue<KIND, kFp8Tiled>(p, R, E, shape, stream);
+  else return enqueue<KIND, kFp8Rows>(p, R, E, shape, stream);
 }
 
-template hipError_t launch_gemm_stream<kGateUp, false>(const GemmParams&, int, int, hipStream_t);
-template hipError_t launch_gemm_stream<kGateUp, true>(const GemmParams&, int, int, hipStream_t);
-template hipError_t launch_gemm_stream<kDownPlainK, false>(const GemmParams&, int, int, hipStream_t);
-template hipError_t launch_gemm_stream<kDownPlainK, true>(const GemmParams&, int, int, hipStream_t);
-template hipError_t launch_gemm_stream<kDownBySlotK, false>(const GemmParams&, int, int, hipStream_t);
-template hipError_t launch_gemm_stream<kDownBySlotK, true>(const GemmParams&, int, int, hipStream_t);
+template hipError_t launch_gemm_stream<kGateUp, false>(const GemmParams&, int, int, StreamShape,
+    hipStream_t);
+template hipError_t launch_gemm_stream<kGateUp, true>(const GemmParams&, int, int, StreamShape,
+    hipStream_t);
+template hipError_t launch_gemm_stream<kDownPlainK, false>(const GemmParams&, int, int, StreamShape,
+    hipStream_t);
+template hipError_t launch_gemm_stream<kDownPlainK, true>(const GemmParams&, int, int, StreamShape,
+    hipStream_t);
+template hipError_t launch_gemm_stream<kDownBySlotK, false>(const GemmParams&, int, int, StreamShape,
+    hipStream_t);
+template hipError_t launch_gemm_stream<kDownBySlotK, true>(const GemmParams&, int, int, StreamShape,
+    hipStream_t);
 
 }  // namespace eaas

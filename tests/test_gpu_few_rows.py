@@ -1,7 +1,7 @@
 """The streaming GEMM kernels of decode-sized batches (a few rows per expert):
-row counts at the edges of their 16-row blocks and 64-row tiles, more than 64
-active experts, and K of one tile, an odd number of 128-channel blocks and
-several ring lengths.
+row counts at the edges of their 16-row blocks and of their 64- and 144-row
+tiles, more than 64 active experts, N that is no multiple of 256, and K of one
+tile, an odd number of 128-channel blocks and several ring lengths.
 
 Against the oracle, and bit for bit against the same tokens inside a batch
 large enough for the tiled kernels (a token's result does not depend on the
@@ -19,11 +19,15 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-2
 
 # rows per expert; the rest of the E experts stay empty.  "alone" has at most
-# two rows per expert on average (one wave per workgroup), "shared" more.
+# two rows per expert on average (one wave per workgroup), "shared" more, and
+# "wide" enough for 144-row blocks (with 64 experts and I 384, more 128-row
+# weight tiles than CUs).
 EDGES = {
     "alone": (128, [33, 17, 16, 15, 2] + [1] * 68),
     "shared": (100, [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 97, 130, 0, 2] + [3] * 60),
     "one expert": (1, [20]),
+    "wide": (64, [143, 144, 145, 288, 289, 96, 97, 112, 113, 128, 129, 1, 16, 17] + [40] * 50),
+    "wide, few tiles": (6, [144, 145, 96, 17, 160, 1]),
 }
 
 
@@ -43,7 +47,7 @@ def run(dev, k, wdt):
 
 @pytest.mark.parametrize("rows", list(EDGES))
 @pytest.mark.parametrize("wdtype", ["bf16", "fp8", "tiled"])
-@pytest.mark.parametrize("H,I", [(128, 128), (384, 256), (1280, 640), (2048, 128)])
+@pytest.mark.parametrize("H,I", [(128, 128), (384, 384), (1280, 640), (2048, 128)])
 def test_row_counts_and_k_lengths(gpu, rows, wdtype, H, I):
     if wdtype == "tiled" and H % 256:
         pytest.skip("the tiled layout needs H a multiple of 256")
@@ -51,7 +55,9 @@ def test_row_counts_and_k_lengths(gpu, rows, wdtype, H, I):
     print(f"few rows: {rows} {wdtype} H={H} I={I} E={E} R={sum(counts)}", flush=True)
     rng = np.random.default_rng(len(counts) + H + I)
     small = rng.permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)
-    big = np.concatenate([small, rng.integers(0, E, 49 * E + 200).astype(np.int32)])
+    # past 120 slots per expert no streaming kernel runs (but for N's last 128 rows)
+    fill = (130 if rows.startswith("wide") else 49) * E + 200
+    big = np.concatenate([small, rng.integers(0, E, fill).astype(np.int32)])
     d = synth.make_inputs(len(big), H, I, E, 1, 77, wdtype="bf16" if wdtype == "bf16" else "fp8")
     d["topk_ids"] = big[:, None].copy()
     d["topk_weights"] = rng.uniform(0.2, 1.0, (len(big), 1)).astype(np.float32)
