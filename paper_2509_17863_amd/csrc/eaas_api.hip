@@ -121,6 +121,23 @@ hipError_t quantize_x(const FfnArgs& a, char* base, const WsLayout& L, hipStream
                               reinterpret_cast<float*>(base + L.xs), hs);
 }
 
+// Routing of `ids` into rt, unless the gate/up launch does it, and (fp8
+// activations) the quantization of x: all that comes before launch_gate_up.
+hipError_t before_gate_up(FfnArgs& a, const int32_t* ids, const eaas_routing& rt, char* base,
+                          const WsLayout& L, hipStream_t hs) {
+  a.perm = rt.perm;
+  a.offsets = rt.offsets;
+  a.active = rt.active;
+  a.ids = ids;
+  a.counts = rt.counts;
+  a.inv = rt.inv;
+  hipError_t e = hipSuccess;
+  if (!gate_up_routes(a))
+    e = launch_route_permute(ids, a.T * a.k, a.E, rt, reinterpret_cast<int32_t*>(base + L.hist),
+                             hs);
+  return e == hipSuccess ? quantize_x(a, base, L, hs) : e;
+}
+
 int hip_status(hipError_t e) { return e == hipSuccess ? EAAS_OK : EAAS_ERR_HIP; }
 
 eaas_routing ws_routing(char* base, const WsLayout& L) {
@@ -309,16 +326,10 @@ int eaas_expert_forward_profiled(const eaas_shape* s, const void* x, const int32
     return hipEventRecord(reinterpret_cast<hipEvent_t>(events[i]), hs);
   };
   if (mark(0) != hipSuccess) return EAAS_ERR_HIP;
-  hipError_t e = launch_route_permute(topk_ids, s->T * s->k, s->E, rt,
-                                      reinterpret_cast<int32_t*>(base + L.hist), hs);
-  if (e != hipSuccess) return EAAS_ERR_HIP;
   float* stage = reinterpret_cast<float*>(base + L.stage);
   FfnArgs a{};
   a.T = s->T; a.H = s->H; a.I = s->I; a.E = s->E; a.k = s->k;
   a.x = static_cast<const uint16_t*>(x);
-  a.perm = rt.perm;
-  a.offsets = rt.offsets;
-  a.active = rt.active;
   a.w_gate_up = w_gate_up;
   a.s_gate_up = w_gate_up_scale;
   a.w_down = w_down;
@@ -329,7 +340,7 @@ int eaas_expert_forward_profiled(const eaas_shape* s, const void* x, const int32
   a.epilogue = kDownBySlot;
   // (fp8 activations: x is quantized in the routing interval, so the gate/up
   // interval times the GEMM alone)
-  e = quantize_x(a, base, L, hs);
+  hipError_t e = before_gate_up(a, topk_ids, rt, base, L, hs);
   if (e != hipSuccess || mark(1) != hipSuccess) return EAAS_ERR_HIP;
   e = launch_gate_up(a, hs);
   if (e != hipSuccess || mark(2) != hipSuccess) return EAAS_ERR_HIP;
@@ -381,17 +392,11 @@ int eaas_expert_forward_segments(const eaas_shape* s, const eaas_segment* segs,
                                    x_cat, ids_cat, w_cat, hs);
   if (e != hipSuccess) return EAAS_ERR_HIP;
   const eaas_routing rt = ws_routing(base, L);
-  e = launch_route_permute(ids_cat, cap * s->k, s->E, rt,
-                           reinterpret_cast<int32_t*>(base + L.hist), hs);
-  if (e != hipSuccess) return EAAS_ERR_HIP;
   float* stage = reinterpret_cast<float*>(base + L.stage);
   FfnArgs a{};
   a.T = cap; a.H = s->H; a.I = s->I; a.E = s->E; a.k = s->k;
   a.capacity = true;
   a.x = x_cat;
-  a.perm = rt.perm;
-  a.offsets = rt.offsets;
-  a.active = rt.active;
   a.w_gate_up = w_gate_up;
   a.s_gate_up = w_gate_up_scale;
   a.w_down = w_down;
@@ -400,7 +405,7 @@ int eaas_expert_forward_segments(const eaas_shape* s, const eaas_segment* segs,
   a.h = reinterpret_cast<uint16_t*>(base + L.h);
   a.y = stage;
   a.epilogue = kDownBySlot;
-  e = quantize_x(a, base, L, hs);
+  e = before_gate_up(a, ids_cat, rt, base, L, hs);
   if (e == hipSuccess) e = launch_gate_up(a, hs);
   if (e == hipSuccess) e = launch_down(a, hs);
   if (e == hipSuccess)
@@ -485,23 +490,17 @@ int eaas_server_step(const eaas_shape* s, const eaas_slot* slots, int n_slots,
                           w_cat, hs);
     if (e != hipSuccess) return EAAS_ERR_HIP;
     const eaas_routing rt = ws_routing(base, L);
-    e = launch_route_permute(ids_cat, cap * g.k, g.E, rt,
-                             reinterpret_cast<int32_t*>(base + L.hist), hs);
-    if (e != hipSuccess) return EAAS_ERR_HIP;
     FfnArgs a{};
     a.T = cap; a.H = g.H; a.I = g.I; a.E = g.E; a.k = g.k;
     a.capacity = true;
     a.x = x_cat;
-    a.perm = rt.perm;
-    a.offsets = rt.offsets;
-    a.active = rt.active;
     set_dtype_args(a, w_dtype, base, L);
     a.h = reinterpret_cast<uint16_t*>(base + L.h);
     a.y = reinterpret_cast<float*>(base + L.stage);
     a.epilogue = kDownBySlot;
     a.layers = layers;
     a.e_layer = s->E;
-    e = quantize_x(a, base, L, hs);
+    e = before_gate_up(a, ids_cat, rt, base, L, hs);
     if (e == hipSuccess) e = launch_gate_up(a, hs);
     if (e == hipSuccess) e = launch_down(a, hs);
     if (e == hipSuccess)

@@ -1565,6 +1565,11 @@ hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N,
   return hipGetLastError();
 }
 
+bool gate_up_routes(const FfnArgs& a) {
+  return a.ids != nullptr && !a.act8 && (long long)a.T * a.k <= kSelfSlots &&
+         stream_shape(a, true) == kStreamFew;
+}
+
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
   // [R,H] x [2I,H]^T -> h [R,I]
   GemmParams g = common_params(a);
@@ -1582,6 +1587,11 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
     g.hq = a.hq;
     g.hs = a.hs;
     return launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
+  }
+  if (gate_up_routes(a)) {
+    g.ids = a.ids;
+    g.counts = a.counts;
+    g.inv = a.inv;
   }
   const StreamShape shape = stream_shape(a, true);
   return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, shape, stream)

@@ -46,6 +46,11 @@ struct GemmParams {
   // weight stages stored contiguously) instead of [E, N, K] row-major
   bool tiled;
   int tn0;                // streaming kernels: first N tile of the launch
+  // a small batch's gate/up launch that routes its rows itself: the slots'
+  // expert ids [R]; it writes counts, offsets, perm, inv and active
+  const int32_t* ids;
+  int32_t* counts;
+  int32_t* inv;
 };
 
 // Weights of group e ([N, K], bf16 or fp8 bytes of esz each).
@@ -116,6 +121,9 @@ __device__ __forceinline__ const void* wave_uniform(const void* p) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo);
 }
+
+// Most slots of a batch whose gate/up launch routes its rows itself.
+constexpr int kSelfSlots = 512;
 
 // The register-streaming kernels (gemm_stream.hip): row blocks of up to 64 rows
 // (one wave or four per workgroup), or of up to 144 rows by 256 or 128 weight

@@ -274,15 +274,25 @@ __device__ __forceinline__ typename Loop::Weights weight_source(const GemmParams
   return s;
 }
 
-// Permuted rows r0 + m (m clamped into [0, rows)): the row of the A operand,
-// and the row of the output.
+// The rows of a block: m of [0, rows) is permuted row r0 + m.  Their slots are
+// in perm, or (self: a launch that routes its rows itself) in LDS.
+struct BlockRows {
+  int r0, rows;
+  bool self;
+  const LDS_AS int* slots;
+};
+// The row of the A operand and the row of the output (m clamped into the block).
 template <int KIND>
-__device__ __forceinline__ int source_row(const GemmParams& p, int r) {
-  return KIND == kGateUp ? min(max(p.perm[r], 0), p.R - 1) / p.k : r;
+__device__ __forceinline__ int source_row(const GemmParams& p, const BlockRows& b, int m) {
+  m = m < b.rows ? m : 0;
+  if (KIND != kGateUp) return b.r0 + m;
+  const int slot = b.self ? b.slots[m] : min(max(p.perm[b.r0 + m], 0), p.R - 1);
+  return slot / p.k;
 }
 template <int KIND>
-__device__ __forceinline__ int output_row(const GemmParams& p, int r) {
-  return KIND == kDownBySlotK ? min(max(p.perm[r], 0), p.R - 1) : r;
+__device__ __forceinline__ int output_row(const GemmParams& p, const BlockRows& b, int m) {
+  m = m < b.rows ? m : 0;
+  return KIND == kDownBySlotK ? min(max(p.perm[b.r0 + m], 0), p.R - 1) : b.r0 + m;
 }
 
 // acc[i][j][v]: token row 16i + lane%16 of the block's `rows`, weight row
@@ -310,9 +320,10 @@ __device__ __forceinline__ void store_rows(const GemmParams& p, int rows, int c0
   }
 }
 
-// Rows [r0, r0 + rows) of expert e (rows <= 16*MB) times this wave's weights.
+// A block of expert e (rows <= 16*MB) times this wave's weights.
 template <int KIND, int W, int MB, int D>
-__device__ __forceinline__ void stream_tile(const GemmParams& p, int e, int r0, int rows, int wt) {
+__device__ __forceinline__ void stream_tile(const GemmParams& p, int e, const BlockRows& b,
+                                            int wt) {
   using Loop = StreamLoop<W, MB, D>;
   const int lane = __lane_id();
   const int l16 = lane & 15, q = lane >> 4;
@@ -326,10 +337,8 @@ __device__ __forceinline__ void stream_tile(const GemmParams& p, int e, int r0, 
   int orow[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
-    const int m = i * 16 + l16;
-    const int r = r0 + (m < rows ? m : 0);
-    orow[i] = output_row<KIND>(p, r);
-    x.off[i] = (uint32_t)source_row<KIND>(p, r) * (uint32_t)(p.lda * 2) + q * 16;
+    orow[i] = output_row<KIND>(p, b, i * 16 + l16);
+    x.off[i] = (uint32_t)source_row<KIND>(p, b, i * 16 + l16) * (uint32_t)(p.lda * 2) + q * 16;
   }
   f32x4 acc[MB][kBlocks];
 #pragma unroll
@@ -337,16 +346,144 @@ __device__ __forceinline__ void stream_tile(const GemmParams& p, int e, int r0, 
 #pragma unroll
     for (int j = 0; j < kBlocks; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   Loop::run(s, x, nk, st, acc);
-  store_rows<KIND, MB>(p, rows, c0, orow, acc);
+  store_rows<KIND, MB>(p, b.rows, c0, orow, acc);
+}
+
+// All rows of an expert, 32 at a time, times one wave's weights.  (A ring of 8 K tiles with 16 rows,
+// 5 with 32: 4 and 3 were within 3%; past 256 registers fewer waves would fit.)
+template <int KIND, int W>
+__device__ __forceinline__ void stream_rows(const GemmParams& p, int e, const BlockRows& all,
+                                            int wt) {
+  constexpr bool FP8 = W != kBf16Rows;
+  for (int m0 = 0; m0 < all.rows; m0 += 32) {
+    const BlockRows b{all.r0 + m0, min(32, all.rows - m0), all.self, all.slots + m0};
+    if (b.rows <= 16) stream_tile<KIND, W, 1, FP8 ? 5 : 8>(p, e, b, wt);
+    else stream_tile<KIND, W, 2, FP8 ? 3 : 5>(p, e, b, wt);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Routing inside the gate/up launch, for batches of at most kSelfSlots slots.
+// The routing launch is 4 to 5 us of such a step (a sixth of the tiny
+// workload's, 7% of one dsv3 token's), and its result is a few ballots away:
+// every wave reads all ids (2 KiB at most), takes the slots of its expert and
+// counts those of the experts before it.  One more workgroup writes the
+// routing arrays that the down projection and the combine read.
+constexpr int kSelfWords = kSelfSlots / kWave;
+
+__device__ __forceinline__ int slot_id(const GemmParams& p, int w) {
+  const int s = w * kWave + __lane_id();
+  const int id = s < p.R ? p.ids[s] : -1;
+  return (unsigned)id < (unsigned)p.E ? id : -1;
+}
+
+// Group g of min(E, R): expert g, or (more experts than slots) the expert of
+// slot g if that is its first slot.  False if the group has no rows.  The
+// expert's slots go to `slots` (written where `writes`) in ascending order.
+__device__ __forceinline__ bool route_self(const GemmParams& p, int g, int* slots, bool writes,
+                                           int& e, BlockRows& b) {
+  int id[kSelfWords];
+#pragma unroll
+  for (int w = 0; w < kSelfWords; ++w) id[w] = w * kWave < p.R ? slot_id(p, w) : -1;
+  e = g;
+  if (p.E > p.R) {
+    e = -1;
+#pragma unroll
+    for (int w = 0; w < kSelfWords; ++w)
+      if (w == g / kWave) e = __builtin_amdgcn_readlane(id[w], g % kWave);
+    if (e < 0) return false;
+  }
+  b.r0 = 0;
+  b.rows = 0;
+  b.self = true;
+  b.slots = (const LDS_AS int*)slots;
+  const uint64_t lt = lanemask_lt();
+  bool first = true;
+#pragma unroll
+  for (int w = 0; w < kSelfWords; ++w) {
+    if (w * kWave >= p.R) break;
+    const uint64_t m = ballot(id[w] == e);
+    if (p.E > p.R && m && b.rows == 0) first = w * kWave + __builtin_ctzll(m) == g;
+    if (writes && id[w] == e) slots[b.rows + __popcll(m & lt)] = w * kWave + __lane_id();
+    b.rows += __popcll(m);
+    b.r0 += __popcll(ballot(id[w] >= 0 && id[w] < e));
+  }
+  // the wave's own LDS writes are read back in order
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return first && b.rows > 0;
+}
+
+// The routing of launch_route_permute, by one wave.
+__device__ __forceinline__ void write_routing(const GemmParams& p, int* next) {
+  const int lane = __lane_id();
+  const uint64_t lt = lanemask_lt();
+  int32_t* offsets = const_cast<int32_t*>(p.offsets);
+  int32_t* active = const_cast<int32_t*>(p.active);
+  int32_t* perm = const_cast<int32_t*>(p.perm);
+  auto wave_sync = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+  for (int e = lane; e < p.E; e += kWave) next[e] = 0;
+  wave_sync();
+  for (int w = 0; w * kWave < p.R; ++w) {
+    const int id = slot_id(p, w);
+    if (id >= 0) atomicAdd(&next[id], 1);
+  }
+  wave_sync();
+  // counts, offsets and the active experts, 64 experts at a time
+  int row = 0, n_active = 0;
+  for (int e0 = 0; e0 < p.E; e0 += kWave) {
+    const int e = e0 + lane;
+    const int c = e < p.E ? next[e] : 0;
+    int incl = c;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int o = __shfl_up(incl, d, kWave);
+      if (lane >= d) incl += o;
+    }
+    const uint64_t act = ballot(c > 0);
+    if (e < p.E) {
+      p.counts[e] = c;
+      offsets[e] = row + incl - c;
+      next[e] = row + incl - c;
+      if (c > 0) active[1 + n_active + __popcll(act & lt)] = e;
+    }
+    row += __shfl(incl, kWave - 1, kWave);
+    n_active += __popcll(act);
+  }
+  if (lane == 0) {
+    offsets[p.E] = row;
+    active[0] = n_active;
+  }
+  for (int a = n_active + lane; a < p.E; a += kWave) active[1 + a] = 0;
+  wave_sync();
+  // stable ranks, 64 slots per step, steps in slot order
+  for (int w = 0; w * kWave < p.R; ++w) {
+    const int s = w * kWave + lane;
+    const int id = slot_id(p, w);
+    uint64_t peers = ballot(id >= 0);
+    for (int bit = 1; bit < p.E; bit <<= 1) {
+      const uint64_t m = ballot(id & bit);
+      peers &= (id & bit) ? m : ~m;
+    }
+    const int rank = __popcll(peers & lt);
+    if (id >= 0) {
+      const int r = next[id] + rank;
+      perm[r] = s;
+      p.inv[s] = r;
+    } else if (s < p.R) {
+      p.inv[s] = -1;
+    }
+    wave_sync();
+    if (id >= 0 && rank == 0) next[id] += __popcll(peers);
+    wave_sync();
+  }
+  for (int r = row + lane; r < p.R; r += kWave) perm[r] = -1;
 }
 
 // grid: min(E, R) * N / 32 waves, one per workgroup: wave wt of the a-th active
-// expert, whose rows it takes 32 at a time.  (A ring of 8 K tiles with 16 rows,
-// 5 with 32: 4 and 3 were within 3%; past 256 registers fewer waves would fit.)
+// expert.
 template <int KIND, int W>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void grouped_gemm_stream_kernel(GemmParams p) {
-  constexpr bool FP8 = W != kBf16Rows;
   const int waves_n = p.N / 32;
   const int a = blockIdx.x / waves_n;
   const int wt = blockIdx.x - a * waves_n;
@@ -355,10 +492,23 @@ void grouped_gemm_stream_kernel(GemmParams p) {
   const int e = min(max(p.active[1 + a], 0), p.E - 1);
   const int r0 = min(max(p.offsets[e], 0), p.R);
   const int end = min(max(p.offsets[e + 1], r0), p.R);
-  for (int r = r0; r < end; r += 32) {
-    if (end - r <= 16) stream_tile<KIND, W, 1, FP8 ? 5 : 8>(p, e, r, end - r, wt);
-    else stream_tile<KIND, W, 2, FP8 ? 3 : 5>(p, e, r, min(32, end - r), wt);
-  }
+  stream_rows<KIND, W>(p, e, BlockRows{r0, end - r0, false, nullptr}, wt);
+}
+
+// Gate/up of a small batch that routes its rows itself (route_self): block 0
+// writes the routing, the others find their own rows.
+template <int W>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void grouped_gemm_stream_self_kernel(GemmParams p) {
+  __shared__ int table[kMaxExperts];
+  if (blockIdx.x == 0) return write_routing(p, table);
+  const int waves_n = p.N / 32;
+  const int g = (blockIdx.x - 1) / waves_n;
+  const int wt = blockIdx.x - 1 - g * waves_n;
+  int e;
+  BlockRows all;
+  if (!route_self(p, g, table, true, e, all)) return;
+  stream_rows<kGateUp, W>(p, e, all, wt);
 }
 
 // ---------------------------------------------------------------------------
@@ -469,8 +619,8 @@ struct SharedLoop {
 };
 
 template <int KIND, int W, int MB, int NW, int CHB, int D>
-__device__ __forceinline__ void shared_tile(const GemmParams& p, int e, int r0, int rows, int wt,
-                                            LDS_AS char* lds) {
+__device__ __forceinline__ void shared_tile(const GemmParams& p, int e, const BlockRows& b,
+                                            int wt, LDS_AS char* lds) {
   using Loop = SharedLoop<W, MB, NW, CHB, D>;
   using S = typename Loop::S;
   const int lane = __lane_id();
@@ -489,22 +639,18 @@ __device__ __forceinline__ void shared_tile(const GemmParams& p, int e, int r0, 
 #pragma unroll
   for (int i = 0; i < Loop::NP; ++i) {
     const int m = threadIdx.x / Loop::LPR + i * Loop::RP;
-    x.off[i] =
-        (uint32_t)source_row<KIND>(p, r0 + (m < rows ? m : 0)) * (uint32_t)(p.lda * 2);
+    x.off[i] = (uint32_t)source_row<KIND>(p, b, m) * (uint32_t)(p.lda * 2);
   }
   int orow[MB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i) {
-    const int m = i * 16 + l16;
-    orow[i] = output_row<KIND>(p, r0 + (m < rows ? m : 0));
-  }
+  for (int i = 0; i < MB; ++i) orow[i] = output_row<KIND>(p, b, i * 16 + l16);
   f32x4 acc[MB][kBlocks];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < kBlocks; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   Loop::run(s, x, nk, st, lds + l16 * Loop::XROW + q * 16, acc);
-  store_rows<KIND, MB>(p, rows, c0, orow, acc);
+  store_rows<KIND, MB>(p, b.rows, c0, orow, acc);
 }
 
 // Row block of a workgroup: the experts' rows in blocks of at most BM rows
@@ -587,12 +733,12 @@ constexpr int kChunk = 512;
 
 // The smallest of shared_tile's row counts that holds the block.
 template <int KIND, int W, class G, int MB>
-__device__ __forceinline__ void tile_of_height(const GemmParams& p, const RowBlock& b, int wt,
-                                               LDS_AS char* lds) {
+__device__ __forceinline__ void tile_of_height(const GemmParams& p, int e, const BlockRows& b,
+                                               int wt, LDS_AS char* lds) {
   if (MB == 1 || b.rows > 16 * (MB - 1))
-    shared_tile<KIND, W, MB, G::NW, kChunk, G::D>(p, b.e, b.r0, b.rows, wt, lds);
+    shared_tile<KIND, W, MB, G::NW, kChunk, G::D>(p, e, b, wt, lds);
   else if constexpr (MB > 1)
-    tile_of_height<KIND, W, G, MB - 1>(p, b, wt, lds);
+    tile_of_height<KIND, W, G, MB - 1>(p, e, b, wt, lds);
 }
 
 // grid: row blocks x N tiles of 32 * NW weight rows, from tile tn0 on.
@@ -605,7 +751,35 @@ void grouped_gemm_shared_kernel(GemmParams p) {
   const int tile = xcd_window_remap(blockIdx.x, gridDim.x);
   if (!locate_rows<ROWS>(p, tile, p.N / (32 * G::NW) - p.tn0, b)) return;
   const int wt = (p.tn0 + b.tn) * G::NW + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  tile_of_height<KIND, W, G, G::MBX>(p, b, wt, (LDS_AS char*)smem);
+  tile_of_height<KIND, W, G, G::MBX>(p, b.e, BlockRows{b.r0, b.rows, false, nullptr}, wt,
+                                     (LDS_AS char*)smem);
+}
+
+// Gate/up of a small batch that routes its rows itself: block 0 writes the
+// routing; workgroup tn of group g takes all of its expert's rows.
+template <int W, class G>
+__global__ __launch_bounds__(kWave * G::NW) __attribute__((amdgpu_waves_per_eu(G::OCC, G::OCC)))
+void grouped_gemm_shared_self_kernel(GemmParams p) {
+  constexpr int ROWS = 16 * G::MBX;
+  __shared__ __attribute__((aligned(16))) char smem[2 * ROWS * (kChunk + 16)];
+  __shared__ int table[kMaxExperts];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  if (blockIdx.x == 0) {
+    if (wave == 0) write_routing(p, table);
+    return;
+  }
+  const int tiles_n = p.N / (32 * G::NW);
+  const int g = (blockIdx.x - 1) / tiles_n;
+  const int tn = blockIdx.x - 1 - g * tiles_n;
+  int e;
+  BlockRows all;
+  if (!route_self(p, g, table, wave == 0, e, all)) return;  // the same answer in every wave
+  for (int m0 = 0; m0 < all.rows; m0 += ROWS) {
+    __syncthreads();  // the slots are written; the last block's rows are read
+    tile_of_height<kGateUp, W, G, G::MBX>(
+        p, e, BlockRows{all.r0 + m0, min(ROWS, all.rows - m0), true, all.slots + m0}, tn * G::NW + wave,
+        (LDS_AS char*)smem);
+  }
 }
 
 template <int KIND, int W, class G>
@@ -625,16 +799,25 @@ template <int KIND, int W>
 hipError_t enqueue(const GemmParams& p, int R, int E, StreamShape shape, hipStream_t stream) {
   if (shape == kStreamWide8) return launch_shared<KIND, W, Wide8<W>>(p, R, E, stream);
   if (shape == kStreamWide4) return launch_shared<KIND, W, Wide4<W>>(p, R, E, stream);
+  const bool self = KIND == kGateUp && p.ids != nullptr;
   // one wave per workgroup up to two rows per expert on average: with the
   // waves of 1 to 16 tokens its start-up is shorter (qwen3, 1 token: gate/up
   // 25 -> 16 us, 16 tokens 108 -> 102); from 2 rows on they are equal, and
   // past 4 the rows that every wave loads by itself cost more
-  if ((long long)R > 2LL * E) return launch_shared<KIND, W, Few<W>>(p, R, E, stream);
-  const long long grid = (long long)std::min(E, R) * (p.N / 32);
+  if ((long long)R > 2LL * E && !self) return launch_shared<KIND, W, Few<W>>(p, R, E, stream);
+  const int waves = (long long)R > 2LL * E ? Few<W>::NW : 1;
+  const long long grid = (long long)std::min(E, R) * (p.N / (32 * waves)) + self;
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((grouped_gemm_stream_kernel<KIND, W>), dim3((unsigned)grid), dim3(kWave), 0,
-                     stream, p);
+  if (!self)
+    hipLaunchKernelGGL((grouped_gemm_stream_kernel<KIND, W>), dim3((unsigned)grid), dim3(kWave), 0,
+                       stream, p);
+  else if (waves == 1)
+    hipLaunchKernelGGL((grouped_gemm_stream_self_kernel<W>), dim3((unsigned)grid), dim3(kWave), 0,
+                       stream, p);
+  else
+    hipLaunchKernelGGL((grouped_gemm_shared_self_kernel<W, Few<W>>), dim3((unsigned)grid),
+                       dim3(kWave * waves), 0, stream, p);
   return hipGetLastError();
 }
 

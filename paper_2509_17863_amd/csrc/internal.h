@@ -55,6 +55,11 @@ struct FfnArgs {
   float* hs = nullptr;          // [R,I/128]
   // fp8 weights stored in the tiled layout of launch_tile_weights_fp8
   bool tiled = false;
+  // set by the caller: the slots' expert ids [R] and the rest of the routing
+  // arrays, for a gate/up launch that routes its rows itself
+  const int32_t* ids = nullptr;
+  int32_t* counts = nullptr;
+  int32_t* inv = nullptr;
   // T is the capacity of a dynamic batch: the batch itself is usually smaller
   bool capacity = false;
 };
@@ -71,6 +76,9 @@ hipError_t launch_quantize_rows(const uint16_t* x, long long rows, int K, uint8_
 hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N, int K, int I,
                                    hipStream_t stream);
 
+// Whether launch_gate_up routes the batch itself (a.ids given, a small decode
+// batch) and writes all routing arrays, so that no routing launch is needed.
+bool gate_up_routes(const FfnArgs& a);
 // Gate/up GEMM with the SiLU*mul epilogue into h.
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream);
 // Down GEMM from h into y (epilogue per a.epilogue).

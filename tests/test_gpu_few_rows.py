@@ -80,3 +80,38 @@ def test_row_counts_and_k_lengths(gpu, rows, wdtype, H, I):
     ref = O.expert_forward(sub)["out"]
     rms = float(np.sqrt((ref ** 2).mean()))
     assert float(np.abs(got - ref).max()) <= TOL * rms
+
+
+@pytest.mark.parametrize("T,k,E", [(1, 8, 32), (1, 1, 1), (2, 8, 1024), (64, 8, 128), (63, 5, 24),
+                                   (64, 8, 32), (4, 8, 33), (128, 4, 65), (512, 1, 512), (3, 2, 2),
+                                   (100, 5, 21), (65, 8, 30)])
+@pytest.mark.parametrize("wdtype", ["bf16", "fp8"])
+def test_routing_of_small_batches(gpu, T, k, E, wdtype):
+    """Up to 512 slots the gate/up launch routes the rows itself: the routing
+    arrays it writes (and the step's output) against the oracle, with masked
+    and repeated ids.  (65 x 8 slots take the routing launch.)"""
+    print(f"small-batch routing T={T} k={k} E={E} {wdtype}", flush=True)
+    H, I, R = 128, 128, T * k
+    d = synth.make_inputs(T, H, I, E, min(k, E), 5 * T + E, wdtype=wdtype)
+    rng = np.random.default_rng(T + k + E)
+    ids = rng.integers(0, E, (T, k)).astype(np.int32)  # repeated ids within a token, too
+    ids[rng.random((T, k)) < 0.2] = -1
+    ids[rng.random((T, k)) < 0.1] = E
+    d.update(k=k, topk_ids=ids, topk_weights=rng.uniform(0.1, 1.0, (T, k)).astype(np.float32))
+    dev = to_device(d)
+    wdt = eaas.EAAS_BF16 if wdtype == "bf16" else eaas.EAAS_FP8_E4M3
+    ws = eaas.alloc_workspace(T, H, I, E, k, wdt)
+    ws.fill_(0xFF)
+    r = eaas.alloc_routing(T, k, E)
+    for t in r.values():
+        t.fill_(-7)
+    out = torch.full((T, H), float("nan"), dtype=torch.float32, device="cuda")
+    eaas.eaas_expert_forward(dev["x"], dev["topk_ids"], dev["topk_weights"], dev["w_gate_up"],
+                             dev["w_down"], out, ws, dev["w_gate_up_scale"], dev["w_down_scale"],
+                             routing=r)
+    torch.cuda.synchronize()
+    ref = O.expert_forward(d)
+    for key, n in (("counts", E), ("offsets", E + 1), ("perm", R), ("inv", R), ("active", E + 1)):
+        assert np.array_equal(r[key].cpu().numpy()[:n], ref["routing"][key]), key
+    rms = float(np.sqrt((ref["out"] ** 2).mean()))
+    assert float(np.abs(out.cpu().numpy() - ref["out"]).max()) <= TOL * rms + (rms == 0.0)
