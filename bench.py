@@ -54,7 +54,7 @@ def gate_up_kernel_name(d: dict) -> str:
     """The gate/up kernel the library dispatches for this workload's shape."""
     T, I, E, k = d["T"], d["I"], d["E"], d["k"]
     if d.get("act8"):
-        return "grouped_gemm_w8a8_kernel<gate/up>"
+        return f"grouped_gemm_{'stream_a8' if T <= 4 else 'w8a8'}_kernel<gate/up>"
     fp8, R = d["wdtype"] == "fp8", T * k
     if R <= (32 if fp8 else 24) * E:
         return f"grouped_gemm_{'stream' if R <= 2 * E else 'shared'}_kernel<gate/up, {d['wdtype']}>"

@@ -1081,7 +1081,6 @@ hipError_t launch_pp(const GemmParams& p, int R, int E, hipStream_t stream) {
 // A has 2 LDS stages and B 3; a stage is refilled only after both groups have
 // read it.  The gate/up epilogue quantizes h per row over the tile's 128 h
 // columns (the 4 waves of a group combine their row maxima in LDS).
-typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 // One wave-wide 4-byte-per-lane DMA (row scales): lane l's 4 bytes at
 // base + voff(l) land at LDS byte address lds + 4*l.
@@ -1552,6 +1551,18 @@ StreamShape stream_shape(const FfnArgs& a, bool gateup) {
   return a.fp8 && gateup ? kStreamWide8 : kNotStreamed;
 }
 
+// fp8 activations: the streaming kernel takes the gate/up GEMM of up to 4
+// tokens and the down GEMM of up to 16, where an expert has one 16-row block.
+// Gate/up has the same workgroups per 128 columns of h either way, so it gains
+// little and loses where an expert's rows differ in every wave's loads (dsv3
+// shape, ids of 8 servers, 8 tokens: 94 us per step tiled, 96 with both
+// streamed; Zipf 1.2, 16 tokens: 207 and 218).  The down GEMM has 256-row
+// tiles to spread over the chip.  Steps, tiled -> streaming, same run: mixtral
+// shape 1 token 162 -> 86 us, 4 tokens 248 -> 186, 16 tokens 328 -> 296; qwen3
+// shape 42 -> 32, 48 -> 40, 118 -> 105; dsv3 shape 92 -> 88, 203 -> 191,
+// 247 -> 229, with Zipf 1.2 routing 207 -> 199.
+bool stream_act8(const FfnArgs& a, bool gateup) { return a.T <= (gateup ? 4 : 16); }
+
 }  // namespace
 
 hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N, int K, int I,
@@ -1566,8 +1577,15 @@ hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N,
 }
 
 bool gate_up_routes(const FfnArgs& a) {
-  return a.ids != nullptr && !a.act8 && (long long)a.T * a.k <= kSelfSlots &&
-         stream_shape(a, true) == kStreamFew;
+  const long long R = (long long)a.T * a.k;
+  if (a.ids == nullptr || R > kSelfSlots) return false;
+  if (!a.act8) return stream_shape(a, true) == kStreamFew;
+  // Only where one workgroup per CU covers every slot's columns: the groups
+  // without rows are not compacted away, and with more workgroups than CUs the
+  // ones that have work pile up on some of them (dsv3 shape, 16 tokens with
+  // ids of 8 servers: 167 us, compacted by the routing launch 119, tiled 125;
+  // qwen3 shape, 16 tokens, Zipf 1.2: 59, tiled 51).
+  return stream_act8(a, true) && R <= a.E && R * (2 * a.I / 256) <= 256;
 }
 
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
@@ -1586,13 +1604,15 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
     g.a_scale = a.xs;
     g.hq = a.hq;
     g.hs = a.hs;
-    return launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
   }
   if (gate_up_routes(a)) {
     g.ids = a.ids;
     g.counts = a.counts;
     g.inv = a.inv;
   }
+  if (a.act8)
+    return stream_act8(a, true) ? launch_gemm_stream_a8<kGateUp>(g, R, a.E, stream)
+                          : launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
   const StreamShape shape = stream_shape(a, true);
   return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, shape, stream)
                : launch_kind<kGateUp, false>(g, R, a.E, shape, stream);
@@ -1613,6 +1633,9 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
   if (a.act8) {
     g.a8 = a.hq;
     g.a_scale = a.hs;
+    if (stream_act8(a, false))
+      return a.epilogue == kDownBySlot ? launch_gemm_stream_a8<kDownBySlotK>(g, R, a.E, stream)
+                                       : launch_gemm_stream_a8<kDownPlainK>(g, R, a.E, stream);
     return a.epilogue == kDownBySlot ? launch_w8a8<kDownBySlotK>(g, R, a.E, small_rows(a), stream)
                                      : launch_w8a8<kDownPlainK>(g, R, a.E, small_rows(a), stream);
   }

@@ -12,6 +12,8 @@ namespace eaas {
 #define CONST_AS __attribute__((address_space(4)))  // read-only global data, scalar loads
 #define GLOBAL_AS __attribute__((address_space(1)))
 
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
 enum GemmKind { kGateUp = 0, kDownPlainK = 1, kDownBySlotK = 2 };
 
 struct GemmParams {
@@ -132,5 +134,8 @@ enum StreamShape { kNotStreamed = 0, kStreamFew = 1, kStreamWide8 = 2, kStreamWi
 template <int KIND, bool FP8>
 hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, StreamShape shape,
                               hipStream_t stream);
+// The same for fp8 weights times fp8 activations (row-major weights).
+template <int KIND>
+hipError_t launch_gemm_stream_a8(const GemmParams& p, int R, int E, hipStream_t stream);
 
 }  // namespace eaas

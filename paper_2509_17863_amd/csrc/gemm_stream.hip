@@ -67,8 +67,8 @@ __device__ __forceinline__ void swap_reg_lane4(uint32_t& lo, uint32_t& hi) {
   hi = r[1];
 }
 
-// Weight layouts: bf16 rows, fp8 rows, fp8 tiled.
-enum StreamWeights { kBf16Rows = 0, kFp8Rows = 1, kFp8Tiled = 2 };
+// Weight layouts: bf16 rows, fp8 rows, fp8 tiled; fp8 rows times fp8 activations.
+enum StreamWeights { kBf16Rows = 0, kFp8Rows = 1, kFp8Tiled = 2, kFp8A8 = 3 };
 
 // A K tile is 128 bytes of each weight row.  MFMA wants lane l to hold row
 // l%16 and 16-byte chunks l/16, l/16 + 4 (bf16) or 8-byte pieces l/16,
@@ -76,14 +76,15 @@ enum StreamWeights { kBf16Rows = 0, kFp8Rows = 1, kFp8Tiled = 2 };
 // or 32 bytes of 16 rows at a time.  So each load takes whole 128-byte lines
 // (8 rows; tiled fp8: 16 rows of 64 contiguous bytes, 1 KiB in all), and the
 // chunks are put in place by swapping register-index bits with lane-index
-// bits just before the MFMAs.
+// bits just before the MFMAs.  (fp8 activations: v_mfma_scale_f32_16x16x128
+// takes the whole K tile, chunks 2*(l/16) and 2*(l/16) + 1 in lane l.)
 constexpr int kBlocks = 2;  // 16-row weight blocks of a wave
 
 template <int W, int MB, int D>
 struct StreamLoop {
-  static constexpr bool FP8 = W != kBf16Rows, kTiled = W == kFp8Tiled;
+  static constexpr bool FP8 = W != kBf16Rows, kTiled = W == kFp8Tiled, A8 = W == kFp8A8;
   static constexpr int KT = FP8 ? 128 : 64;  // channels per K tile
-  static constexpr int KS = KT / 32;         // MFMA k-steps per K tile
+  static constexpr int KS = A8 ? 2 : KT / 32;  // MFMA k-steps per K tile (A8: 16-byte chunks)
 
   struct Weights {
     const GLOBAL_AS uint8_t* w;  // the expert's (wave-uniform)
@@ -95,11 +96,14 @@ struct StreamLoop {
   struct Rows {
     const uint8_t* x;        // wave-uniform
     uint32_t off[MB];        // per lane
+    const float* xs;         // A8: row scales, wave-uniform
+    uint32_t soff[MB];       // A8: per lane, index of the row's first scale
   };
   struct Stage {
     u32x4 w[kBlocks][2];
     float sc[kBlocks];
     bf16x8 x[MB][KS];        // not used where the rows come through LDS
+    float xs[MB];            // A8
   };
 
   // Byte offset inside the K tile and row that lane l loads for block row 0.
@@ -110,6 +114,7 @@ struct StreamLoop {
     const int b3 = (lane >> 3) & 1, b4 = (lane >> 4) & 1, b5 = lane >> 5;
     if (W == kFp8Tiled) return 16 * (2 * b4 + b5);          // lane bits 5,4 = piece bits 1,2
     if (W == kFp8Rows) return 16 * (4 * b4 + 2 * b3 + b5);  // bits 5,4,3 = piece bits 1,3,2
+    if (A8) return 16 * (4 * b5 + 2 * b4 + b3);             // bits 5,4,3 = chunk bits 2,1,0
     return 16 * (4 * b3 + 2 * b5 + b4);                     // bits 5,4,3 = chunk bits 1,0,2
   }
 
@@ -126,19 +131,23 @@ struct StreamLoop {
     }
   }
   static __device__ __forceinline__ void load_x(const Rows& x, int kt, Stage& f) {
-    const uint8_t* xk = x.x + (size_t)kt * (KT * 2);
+    const uint8_t* xk = x.x + (size_t)kt * (A8 ? KT : KT * 2);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int i = 0; i < MB; ++i)
-        f.x[i][ks] = *reinterpret_cast<const bf16x8*>(xk + ks * 64 + x.off[i]);
+        f.x[i][ks] = *reinterpret_cast<const bf16x8*>(xk + ks * (A8 ? 16 : 64) + x.off[i]);
+    if constexpr (A8) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i) f.xs[i] = x.xs[x.soff[i] + (uint32_t)kt];
+    }
   }
 
   // The block's weight fragment of each k-step.
   static __device__ __forceinline__ void fragments(const u32x4 (&w)[2], bf16x8 (&f)[KS]) {
     u32x4 a = w[0], b = w[1];
-    if constexpr (W == kBf16Rows) {
-      // register = row bit 3, lane bits 5,4,3 = chunk bits 1,0,2
+    if constexpr (W == kBf16Rows || A8) {
+      // register = row bit 3, lane bit 3 = chunk bit 2 (A8: 0)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         uint32_t lo = a[i], hi = b[i];
@@ -174,8 +183,33 @@ struct StreamLoop {
     }
   }
 
+  static __device__ __forceinline__ i32x8 chunk_pair(const bf16x8 (&c)[KS]) {
+    const u32x4 lo = __builtin_bit_cast(u32x4, c[0]), hi = __builtin_bit_cast(u32x4, c[1]);
+    return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
+                 (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+  }
   static __device__ __forceinline__ void multiply(const Stage& f, f32x4 (&acc)[MB][kBlocks]) {
-    if constexpr (FP8) {
+    if constexpr (A8) {
+      i32x8 w[kBlocks];
+#pragma unroll
+      for (int j = 0; j < kBlocks; ++j) {
+        bf16x8 c[KS];
+        fragments(f.w[j], c);
+        w[j] = chunk_pair(c);
+      }
+#pragma unroll
+      for (int i = 0; i < MB; ++i) {
+        const i32x8 x = chunk_pair(f.x[i]);
+#pragma unroll
+        for (int j = 0; j < kBlocks; ++j) {
+          const f32x4 part = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+              w[j], x, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0, 127, 0, 127);
+          const float s = f.xs[i] * f.sc[j];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[i][j][v] += s * part[v];
+        }
+      }
+    } else if constexpr (FP8) {
 #pragma unroll
       for (int j = 0; j < kBlocks; ++j) {
         bf16x8 w[KS];
@@ -320,10 +354,50 @@ __device__ __forceinline__ void store_rows(const GemmParams& p, int rows, int c0
   }
 }
 
+// fp8 activations, gate/up: h quantized per row and 128 columns, which are the
+// workgroup's eight waves' (red: [16 * MB][8] in LDS).
+constexpr int kA8Waves = 8;
+template <int MB>
+__device__ __forceinline__ void store_rows_a8(const GemmParams& p, int rows, int c0,
+                                              const int (&orow)[MB],
+                                              const f32x4 (&acc)[MB][kBlocks],
+                                              LDS_AS float* red) {
+  const int lane = __lane_id();
+  const int l16 = lane & 15, q = lane >> 4;
+  const int wave = c0 / 16 % kA8Waves;
+  float hv[MB][4];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    float m = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float h = silu_mul(acc[i][0][v], acc[i][1][v]);
+      hv[i][v] = __uint_as_float(f32_to_bf16_bits(h) << 16);
+      m = fmaxf(m, fabsf(hv[i][v]));
+    }
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    if (q == 0) red[(i * 16 + l16) * kA8Waves + wave] = m;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int m0 = i * 16 + l16;
+    if (m0 >= rows) continue;
+    float m = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kA8Waves; ++w) m = fmaxf(m, red[m0 * kA8Waves + w]);
+    const float s = m > 0.0f ? m / 448.0f : 1.0f;
+    *reinterpret_cast<uint32_t*>(p.hq + (size_t)orow[i] * p.I + c0 + 4 * q) =
+        pack_e4m3x4(hv[i][0] / s, hv[i][1] / s, hv[i][2] / s, hv[i][3] / s);
+    if (wave == 0 && q == 0) p.hs[(size_t)orow[i] * (p.I / 128) + c0 / 128] = s;
+  }
+}
+
 // A block of expert e (rows <= 16*MB) times this wave's weights.
 template <int KIND, int W, int MB, int D>
 __device__ __forceinline__ void stream_tile(const GemmParams& p, int e, const BlockRows& b,
-                                            int wt) {
+                                            int wt, LDS_AS float* red) {
   using Loop = StreamLoop<W, MB, D>;
   const int lane = __lane_id();
   const int l16 = lane & 15, q = lane >> 4;
@@ -333,12 +407,15 @@ __device__ __forceinline__ void stream_tile(const GemmParams& p, int e, const Bl
   typename Loop::Stage st[D];
   Loop::start(s, nk, st);
   typename Loop::Rows x;
-  x.x = reinterpret_cast<const uint8_t*>(p.a);
+  x.x = Loop::A8 ? p.a8 : reinterpret_cast<const uint8_t*>(p.a);
+  x.xs = p.a_scale;
   int orow[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
     orow[i] = output_row<KIND>(p, b, i * 16 + l16);
-    x.off[i] = (uint32_t)source_row<KIND>(p, b, i * 16 + l16) * (uint32_t)(p.lda * 2) + q * 16;
+    const uint32_t row = (uint32_t)source_row<KIND>(p, b, i * 16 + l16);
+    x.off[i] = row * (uint32_t)(Loop::A8 ? p.lda : p.lda * 2) + q * (Loop::A8 ? 32 : 16);
+    x.soff[i] = row * (uint32_t)nk;
   }
   f32x4 acc[MB][kBlocks];
 #pragma unroll
@@ -346,7 +423,8 @@ __device__ __forceinline__ void stream_tile(const GemmParams& p, int e, const Bl
 #pragma unroll
     for (int j = 0; j < kBlocks; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   Loop::run(s, x, nk, st, acc);
-  store_rows<KIND, MB>(p, b.rows, c0, orow, acc);
+  if constexpr (Loop::A8 && KIND == kGateUp) store_rows_a8<MB>(p, b.rows, c0, orow, acc, red);
+  else store_rows<KIND, MB>(p, b.rows, c0, orow, acc);
 }
 
 // All rows of an expert, 32 at a time, times one wave's weights.  (A ring of 8 K tiles with 16 rows,
@@ -357,8 +435,8 @@ __device__ __forceinline__ void stream_rows(const GemmParams& p, int e, const Bl
   constexpr bool FP8 = W != kBf16Rows;
   for (int m0 = 0; m0 < all.rows; m0 += 32) {
     const BlockRows b{all.r0 + m0, min(32, all.rows - m0), all.self, all.slots + m0};
-    if (b.rows <= 16) stream_tile<KIND, W, 1, FP8 ? 5 : 8>(p, e, b, wt);
-    else stream_tile<KIND, W, 2, FP8 ? 3 : 5>(p, e, b, wt);
+    if (b.rows <= 16) stream_tile<KIND, W, 1, FP8 ? 5 : 8>(p, e, b, wt, nullptr);
+    else stream_tile<KIND, W, 2, FP8 ? 3 : 5>(p, e, b, wt, nullptr);
   }
 }
 
@@ -795,6 +873,56 @@ hipError_t launch_shared(const GemmParams& p, int R, int E, hipStream_t stream) 
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// fp8 weights and activations, one row block of 16 rows: every wave loads its
+// token rows like its weights (half the bytes of bf16 rows, read through L2);
+// the eight waves of a gate/up workgroup own the 128 columns of h that share a
+// scale.  (Blocks of 32 and 64 rows, for batches of up to 24 slots per expert,
+// gained 3 to 20% on even routing but lost up to 3.5x where a few experts get
+// most of the rows: qwen3, 384 tokens, Zipf 1.2: 126 -> 444 us.)
+constexpr int kA8Rows = 16;
+template <int KIND>
+__device__ __forceinline__ void stream_rows_a8(const GemmParams& p, int e, const BlockRows& all,
+                                               int wt, LDS_AS float* red) {
+  for (int m0 = 0; m0 < all.rows; m0 += kA8Rows) {
+    const BlockRows b{all.r0 + m0, min(kA8Rows, all.rows - m0), all.self, all.slots + m0};
+    if (KIND == kGateUp) __syncthreads();  // the slots are written; the last block's maxima are read
+    stream_tile<KIND, kFp8A8, 1, 5>(p, e, b, wt, red);
+  }
+}
+
+// grid: min(E, R) experts x N / (32 * waves) workgroups; SELF (gate/up): block
+// 0 writes the routing, the others find their own rows.
+template <int KIND, bool SELF>
+__global__ __launch_bounds__(kWave * (KIND == kGateUp ? kA8Waves : 1))
+__attribute__((amdgpu_waves_per_eu(2, 2)))
+void grouped_gemm_stream_a8_kernel(GemmParams p) {
+  constexpr int NW = KIND == kGateUp ? kA8Waves : 1;
+  __shared__ float red[KIND == kGateUp ? kA8Rows * kA8Waves : 1];
+  __shared__ int table[SELF ? kMaxExperts : 1];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  if (SELF && blockIdx.x == 0) {
+    if (wave == 0) write_routing(p, table);
+    return;
+  }
+  const int bid = blockIdx.x - SELF;
+  const int tiles_n = p.N / (32 * NW);
+  const int a = bid / tiles_n;
+  const int wt = (bid - a * tiles_n) * NW + wave;
+  int e;
+  BlockRows all;
+  if constexpr (SELF) {
+    if (!route_self(p, a, table, wave == 0, e, all)) return;  // the same answer in every wave
+  } else {
+    // routing arrays may come from the caller: clamp every index taken from them
+    if (a >= min(max(p.active[0], 0), p.E)) return;
+    e = min(max(p.active[1 + a], 0), p.E - 1);
+    const int r0 = min(max(p.offsets[e], 0), p.R);
+    all = BlockRows{r0, min(max(p.offsets[e + 1], r0), p.R) - r0, false, nullptr};
+  }
+  stream_rows_a8<KIND>(p, e, all, wt, (LDS_AS float*)red);
+}
+
 template <int KIND, int W>
 hipError_t enqueue(const GemmParams& p, int R, int E, StreamShape shape, hipStream_t stream) {
   if (shape == kStreamWide8) return launch_shared<KIND, W, Wide8<W>>(p, R, E, stream);
@@ -822,6 +950,26 @@ hipError_t enqueue(const GemmParams& p, int R, int E, StreamShape shape, hipStre
 }
 
 }  // namespace
+
+template <int KIND>
+hipError_t launch_gemm_stream_a8(const GemmParams& p, int R, int E, hipStream_t stream) {
+  constexpr int NW = KIND == kGateUp ? kA8Waves : 1;
+  const bool self = KIND == kGateUp && p.ids != nullptr;
+  if (p.N % (32 * NW)) return hipErrorInvalidValue;
+  const long long grid = (long long)std::min(E, R) * (p.N / (32 * NW)) + self;
+  if (grid <= 0) return hipSuccess;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (self)
+    hipLaunchKernelGGL((grouped_gemm_stream_a8_kernel<KIND, KIND == kGateUp>),
+                       dim3((unsigned)grid), dim3(kWave * NW), 0, stream, p);
+  else
+    hipLaunchKernelGGL((grouped_gemm_stream_a8_kernel<KIND, false>), dim3((unsigned)grid),
+                       dim3(kWave * NW), 0, stream, p);
+  return hipGetLastError();
+}
+template hipError_t launch_gemm_stream_a8<kGateUp>(const GemmParams&, int, int, hipStream_t);
+template hipError_t launch_gemm_stream_a8<kDownPlainK>(const GemmParams&, int, int, hipStream_t);
+template hipError_t launch_gemm_stream_a8<kDownBySlotK>(const GemmParams&, int, int, hipStream_t);
 
 template <int KIND, bool FP8>
 hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, StreamShape shape,

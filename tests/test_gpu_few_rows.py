@@ -40,6 +40,7 @@ def run(dev, k, wdt):
     out = torch.full((T, H), float("nan"), dtype=torch.float32, device="cuda")
     eaas.eaas_expert_forward(dev["x"], dev["topk_ids"], dev["topk_weights"], dev["w_gate_up"],
                              dev["w_down"], out, ws, dev["w_gate_up_scale"], dev["w_down_scale"],
+                             act8=wdt == eaas.EAAS_FP8_E4M3_A8,
                              tiled=wdt == eaas.EAAS_FP8_E4M3_TILED)
     torch.cuda.synchronize()
     return out.cpu().numpy()
@@ -115,3 +116,30 @@ def test_routing_of_small_batches(gpu, T, k, E, wdtype):
         assert np.array_equal(r[key].cpu().numpy()[:n], ref["routing"][key]), key
     rms = float(np.sqrt((ref["out"] ** 2).mean()))
     assert float(np.abs(out.cpu().numpy() - ref["out"]).max()) <= TOL * rms + (rms == 0.0)
+
+
+@pytest.mark.parametrize("T,k,E", [(1, 1, 1), (1, 8, 32), (4, 8, 33), (4, 64, 8), (5, 2, 2),
+                                   (16, 8, 24), (15, 8, 1024), (16, 40, 64), (16, 64, 1024)])
+@pytest.mark.parametrize("H,I", [(256, 128), (768, 384), (1280, 640), (2048, 1152)])
+def test_fp8_activations_of_few_tokens(gpu, T, k, E, H, I):
+    """fp8 activations: up to 4 (gate/up) or 16 tokens (down) take the streaming
+    kernel, with the routing inside the launch (at most E slots and 256
+    workgroups) and outside, one to several 16-row blocks (repeated ids), K of
+    1 to 16 tiles and masked ids.
+    Bit for bit against the tiled kernel, which takes the same tokens inside a
+    batch of 17."""
+    if E == 1024 and H * I > 256 * 128:
+        pytest.skip("one size is enough for 1024 experts")
+    print(f"few rows a8: T={T} k={k} E={E} H={H} I={I}", flush=True)
+    rng = np.random.default_rng(T + k + E + H)
+    d = synth.make_inputs(17, H, I, E, min(k, E), 78, wdtype="fp8")
+    ids = rng.integers(0, E, (17, k)).astype(np.int32)
+    ids[rng.random((17, k)) < 0.2] = -1
+    d.update(k=k, topk_ids=ids, topk_weights=rng.uniform(0.2, 1.0, (17, k)).astype(np.float32))
+    dev = to_device(d)
+    whole = run(dev, k, eaas.EAAS_FP8_E4M3_A8)
+    few = {key: v[:T].contiguous() if key in ("x", "topk_ids", "topk_weights") else v
+           for key, v in dev.items()}
+    got = run(few, k, eaas.EAAS_FP8_E4M3_A8)
+    assert np.isfinite(got).all()
+    assert np.array_equal(got.view(np.uint32), whole[:T].view(np.uint32))
