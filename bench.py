@@ -52,22 +52,25 @@ def algorithmic(d: dict, counts: np.ndarray) -> dict:
 
 def gate_up_kernel_name(d: dict) -> str:
     """The gate/up kernel the library dispatches for this workload's shape."""
-    T, I, E, k = d["T"], d["I"], d["E"], d["k"]
-    if d.get("act8"):
-        return f"grouped_gemm_{'stream_a8' if T <= 4 else 'w8a8'}_kernel<gate/up>"
-    fp8, R = d["wdtype"] == "fp8", T * k
-    if R <= (32 if fp8 else 24) * E:
-        return f"grouped_gemm_{'stream' if R <= 2 * E else 'shared'}_kernel<gate/up, {d['wdtype']}>"
-    if R <= 120 * E and (fp8 or E * (2 * I // 128) <= 256):
-        return f"grouped_gemm_shared_kernel<gate/up, {d['wdtype']}, 144 rows>"
-    if fp8:
-        return "grouped_gemm_dma_kernel<gate/up, fp8 weights>"
-    return "grouped_gemm_pp_kernel<gate/up>"
+    from paper_2509_17863_amd import eaas
+
+    fp8 = d["wdtype"] == "fp8"
+    wdt = eaas.EAAS_BF16 if not fp8 else \
+        eaas.EAAS_FP8_E4M3_A8 if d.get("act8") else eaas.EAAS_FP8_E4M3
+    path, _ = eaas._gemm_plan(d["T"], d["H"], d["I"], d["E"], d["k"], wdt, True)
+    return {"tiled": "grouped_gemm_dma_kernel<gate/up, fp8 weights>" if fp8
+            else "grouped_gemm_pp_kernel<gate/up>",
+            "one_wave": f"grouped_gemm_stream_kernel<gate/up, {d['wdtype']}>",
+            "few": f"grouped_gemm_shared_kernel<gate/up, {d['wdtype']}>",
+            "wide8": f"grouped_gemm_shared_kernel<gate/up, {d['wdtype']}, 144 rows>",
+            "wide4": f"grouped_gemm_shared_kernel<gate/up, {d['wdtype']}, 144 rows>",
+            "tiled_a8": "grouped_gemm_w8a8_kernel<gate/up>",
+            "stream_a8": "grouped_gemm_stream_a8_kernel<gate/up>"}[path]
 
 
 def kernel_source_sha256() -> str:
     h = hashlib.sha256()
-    for f in ("gemm.hip", "gemm_stream.hip", "gemm_common.h", "common.h", "internal.h"):
+    for f in ("gemm.hip", "gemm_stream.hip", "gemm_common.h", "dispatch.h", "common.h", "internal.h"):
         with open(os.path.join(ROOT, "paper_2509_17863_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

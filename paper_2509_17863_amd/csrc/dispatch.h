@@ -1,0 +1,95 @@
+// Which kernels a batch's two grouped GEMMs take: a function of sizes and
+// weight dtype alone, so that it can be asked without a GPU
+// (eaas_internal_gemm_plan).
+#pragma once
+
+#include "internal.h"
+
+namespace eaas {
+
+enum GemmPath {
+  kPathTiled = 0,     // gemm.hip: LDS-DMA tiles
+  kPathOneWave = 1,   // gemm_stream.hip: one wave per workgroup
+  kPathFew = 2,       // 64-row blocks, four waves
+  kPathWide8 = 3,     // 144-row blocks, eight waves
+  kPathWide4 = 4,     // 144-row blocks, four waves
+  kPathTiledA8 = 5,   // gemm.hip: fp8 activations
+  kPathStreamA8 = 6,  // gemm_stream.hip: fp8 activations
+};
+
+struct GemmPlan {
+  GemmPath path;
+  bool routes;  // gate/up: the launch routes the batch itself if it has the ids
+};
+
+// Most slots of a batch whose gate/up launch routes its rows itself.
+constexpr int kSelfSlots = 512;
+
+// Which batches the streaming kernels of gemm_stream.hip take, by the slots per
+// resident expert.  A dynamic batch passes its capacity, which it rarely fills
+// (and slots of other servers' experts count too), so its limits are higher.
+//
+// Few rows: step times, tiled kernels -> streaming (us), by slots per expert:
+//   bf16: qwen3 shape 2: 226 -> 190, 32: 284 -> 261, 48: 298 -> 289, 64: 312 ->
+//         370; with Zipf 1.1 routing 16: 185 -> 187, 32: 230 -> 252
+//         dsv3 shape 16: 503 -> 466, 32: 519 -> 500, 48: 529 -> 530
+//         mixtral shape 2: 571 -> 444, 32: 626 -> 517
+//   fp8:  dsv3 shape 8: 264 -> 233, 32: 278 -> 268, 48: 293 -> 304; with Zipf
+//         1.2 routing 32: 375 -> 330
+//         mixtral shape 8: 411 -> 259, 48: 469 -> 358
+// One wave per workgroup up to two rows per expert on average: with the waves
+// of 1 to 16 tokens its start-up is shorter (qwen3, 1 token: gate/up 25 -> 16
+// us, 16 tokens 108 -> 102); from 2 rows on they are equal, and past 4 the rows
+// that every wave loads by itself cost more.
+// One 144-row block per expert (up to 120 slots, so that random counts stay
+// below 144): the fp8 gate/up GEMM, whose tiled kernel needs a second tile past
+// 96 rows: dsv3 shape 64 slots 209 -> 182 us, 64 with Zipf 1.2 302 -> 264, 96:
+// 327 -> 239; at 128 it is 336 -> 355.  (The down GEMM's smaller tiled
+// workgroups are as fast: 64: 132 -> 129, 96: 163 -> 159.)
+// The same where 128-row tiles at most fill the chip once, so that the tiled
+// kernels' 256-row ones leave half of it idle: down GEMM, mixtral shape, bf16
+// 64 slots 281 -> 185 us, 128: 288 -> 222, fp8 111: 227 -> 187; a bf16 gate/up
+// of 8 experts x 1 024 rows, 64 slots: 33 -> 27.
+// N no multiple of 256: the streaming kernel alone up to 350 slots per expert
+// or two rounds of its blocks (whole step, H 1920, I 640, E 24, k 6: 200 slots
+// 103 against 101 us with the tiled kernel for N / 256 tiles and the streaming
+// one for the rest, 300: 137 against 131, 500: 201 against 214; H 384, I 128,
+// E 5, k 2, 280 slots: 43 against 32).
+inline GemmPath stream_path(const FfnArgs& a, bool gateup) {
+  const long long R = (long long)a.T * a.k, N = gateup ? 2LL * a.I : a.H;
+  if (R <= (a.capacity ? 48 : a.fp8 ? 32 : 24) * (long long)a.E)
+    return R <= 2LL * a.E ? kPathOneWave : kPathFew;
+  if (N % 256 && (R <= 350LL * a.E || (R / 144 + a.E) * (N / 128) <= 512)) return kPathWide4;
+  if (R > (a.capacity ? 480 : 120) * (long long)a.E) return kPathTiled;
+  if (a.E * (N / 128) <= 256) return kPathWide4;
+  return a.fp8 && gateup ? kPathWide8 : kPathTiled;
+}
+
+// fp8 activations: the streaming kernel takes the gate/up GEMM of up to 4
+// tokens and the down GEMM of up to 16, where an expert has one 16-row block.
+// Gate/up has the same workgroups per 128 columns of h either way, so it gains
+// little and loses where an expert's rows differ in every wave's loads (dsv3
+// shape, ids of 8 servers, 8 tokens: 94 us per step tiled, 96 with both
+// streamed; Zipf 1.2, 16 tokens: 207 and 218).  The down GEMM has 256-row
+// tiles to spread over the chip.  Steps, tiled -> streaming, same run: mixtral
+// shape 1 token 162 -> 86 us, 4 tokens 248 -> 186, 16 tokens 328 -> 296; qwen3
+// shape 42 -> 32, 48 -> 40, 118 -> 105; dsv3 shape 92 -> 88, 203 -> 191,
+// 247 -> 229, with Zipf 1.2 routing 207 -> 199.
+inline GemmPlan gemm_plan(const FfnArgs& a, bool gateup) {
+  const long long R = (long long)a.T * a.k;
+  if (!a.act8) {
+    const GemmPath path = stream_path(a, gateup);
+    return {path, gateup && R <= kSelfSlots && (path == kPathOneWave || path == kPathFew)};
+  }
+  const bool stream = a.T <= (gateup ? 4 : 16);
+  // Routing inside the launch only where one workgroup per CU covers every
+  // slot's columns: the groups without rows are not compacted away, and with
+  // more workgroups than CUs the ones that have work pile up on some of them
+  // (dsv3 shape, 16 tokens with ids of 8 servers: 167 us, compacted by the
+  // routing launch 119, tiled 125; qwen3 shape, 16 tokens, Zipf 1.2: 59, tiled
+  // 51).
+  return {stream ? kPathStreamA8 : kPathTiledA8,
+          gateup && stream && R <= kSelfSlots && R <= a.E && R * (2 * a.I / 256) <= 256};
+}
+
+}  // namespace eaas

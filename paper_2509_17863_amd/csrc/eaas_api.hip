@@ -9,7 +9,7 @@
 #include <mutex>
 
 #include "common.h"
-#include "internal.h"
+#include "dispatch.h"
 
 namespace {
 
@@ -563,6 +563,22 @@ int eaas_expert_forward_noalloc(const eaas_shape* s, const void* x, const int32_
   return eaas_expert_forward_profiled(s, x, topk_ids, topk_weights, w_gate_up, w_gate_up_scale,
                                       w_down, w_down_scale, w_dtype, out, out_dtype, r, ws,
                                       (size_t)EAAS_NOALLOC_SCRATCH_BYTES, stream, nullptr);
+}
+
+// Not part of the ABI: the kernels a batch takes, for tests and measurements.
+// Returns the GemmPath of the GEMM plus 16 if its launch also routes the batch
+// (entry points that take ids), or -1 for what the library rejects.
+int eaas_internal_gemm_plan(const eaas_shape* s, int w_dtype, int capacity, int gate_up) {
+  if (check_shape(s) != EAAS_OK || !known_wdtype(w_dtype) ||
+      check_dtype_shape(s, w_dtype) != EAAS_OK)
+    return -1;
+  FfnArgs a{};
+  a.T = s->T; a.H = s->H; a.I = s->I; a.E = s->E; a.k = s->k;
+  a.fp8 = w_dtype != EAAS_BF16;
+  a.act8 = w_dtype == EAAS_FP8_E4M3_A8;
+  a.capacity = capacity != 0;
+  const GemmPlan plan = gemm_plan(a, gate_up != 0);
+  return (int)plan.path + (plan.routes ? 16 : 0);
 }
 
 const char* eaas_status_string(int status) {

@@ -36,7 +36,7 @@
 // down epilogues stage each wave's accumulators through LDS so the fp32
 // rows go out as whole 256-byte row segments.
 // Batches of a few rows per expert take the streaming kernels of
-// gemm_stream.hip instead (stream_shape below).
+// gemm_stream.hip instead (dispatch.h).
 // LDS rows are BK elements long; 16-byte chunk c of row r is stored at chunk
 // c ^ swz(r) so 32-row fragment reads hit every bank once.
 //
@@ -52,6 +52,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "dispatch.h"
 #include "gemm_common.h"
 
 namespace eaas {
@@ -1480,8 +1481,8 @@ __global__ __launch_bounds__(256) void tile_weights_fp8_kernel(const uint8_t* __
 // They cover N / 256 whole tiles; of an N that is no multiple of 256 the last
 // 128 rows go to the streaming kernel.
 template <int KIND, bool FP8>
-hipError_t launch_kind(GemmParams p, int R, int E, StreamShape shape, hipStream_t stream) {
-  if (shape != kNotStreamed) return launch_gemm_stream<KIND, FP8>(p, R, E, shape, stream);
+hipError_t launch_kind(GemmParams p, int R, int E, GemmPath path, hipStream_t stream) {
+  if (path != kPathTiled) return launch_gemm_stream<KIND, FP8>(p, R, E, path, stream);
   hipError_t e;
   if constexpr (!FP8)
     e = launch_pp<KIND>(p, R, E, stream);
@@ -1493,7 +1494,7 @@ hipError_t launch_kind(GemmParams p, int R, int E, StreamShape shape, hipStream_
     e = launch_dma<KIND, true, 64, 3, 3, 1, 1, 4, 3, 2>(p, R, E, stream);
   if (e != hipSuccess || p.N % 256 == 0) return e;
   p.tn0 = p.N / 256 * 2;
-  return launch_gemm_stream<KIND, FP8>(p, R, E, kStreamWide4, stream);
+  return launch_gemm_stream<KIND, FP8>(p, R, E, kPathWide4, stream);
 }
 
 GemmParams common_params(const FfnArgs& a) {
@@ -1516,53 +1517,6 @@ bool small_rows(const FfnArgs& a) {
   return (long long)a.T * a.k <= 128LL * a.E;
 }
 
-// Which batches the streaming kernels of gemm_stream.hip take, by the slots per
-// resident expert.  A dynamic batch passes its capacity, which it rarely fills
-// (and slots of other servers' experts count too), so its limits are higher.
-//
-// Few rows: step times, tiled kernels -> streaming (us), by slots per expert:
-//   bf16: qwen3 shape 2: 226 -> 190, 32: 284 -> 261, 48: 298 -> 289, 64: 312 ->
-//         370; with Zipf 1.1 routing 16: 185 -> 187, 32: 230 -> 252
-//         dsv3 shape 16: 503 -> 466, 32: 519 -> 500, 48: 529 -> 530
-//         mixtral shape 2: 571 -> 444, 32: 626 -> 517
-//   fp8:  dsv3 shape 8: 264 -> 233, 32: 278 -> 268, 48: 293 -> 304; with Zipf
-//         1.2 routing 32: 375 -> 330
-//         mixtral shape 8: 411 -> 259, 48: 469 -> 358
-// One 144-row block per expert (up to 120 slots, so that random counts stay
-// below 144): the fp8 gate/up GEMM, whose tiled kernel needs a second tile past
-// 96 rows: dsv3 shape 64 slots 209 -> 182 us, 64 with Zipf 1.2 302 -> 264, 96:
-// 327 -> 239; at 128 it is 336 -> 355.  (The down GEMM's smaller tiled
-// workgroups are as fast: 64: 132 -> 129, 96: 163 -> 159.)
-// The same where 128-row tiles at most fill the chip once, so that the tiled
-// kernels' 256-row ones leave half of it idle: down GEMM, mixtral shape, bf16
-// 64 slots 281 -> 185 us, 128: 288 -> 222, fp8 111: 227 -> 187; a bf16 gate/up
-// of 8 experts x 1 024 rows, 64 slots: 33 -> 27.
-// N no multiple of 256: the streaming kernel alone up to 350 slots per expert
-// or two rounds of its blocks (whole step, H 1920, I 640, E 24, k 6: 200 slots
-// 103 against 101 us with the tiled kernel for N / 256 tiles and the streaming
-// one for the rest, 300: 137 against 131, 500: 201 against 214; H 384, I 128,
-// E 5, k 2, 280 slots: 43 against 32).
-StreamShape stream_shape(const FfnArgs& a, bool gateup) {
-  const long long R = (long long)a.T * a.k, N = gateup ? 2LL * a.I : a.H;
-  if (R <= (a.capacity ? 48 : a.fp8 ? 32 : 24) * (long long)a.E) return kStreamFew;
-  if (N % 256 && (R <= 350LL * a.E || (R / 144 + a.E) * (N / 128) <= 512)) return kStreamWide4;
-  if (R > (a.capacity ? 480 : 120) * (long long)a.E) return kNotStreamed;
-  if (a.E * (N / 128) <= 256) return kStreamWide4;
-  return a.fp8 && gateup ? kStreamWide8 : kNotStreamed;
-}
-
-// fp8 activations: the streaming kernel takes the gate/up GEMM of up to 4
-// tokens and the down GEMM of up to 16, where an expert has one 16-row block.
-// Gate/up has the same workgroups per 128 columns of h either way, so it gains
-// little and loses where an expert's rows differ in every wave's loads (dsv3
-// shape, ids of 8 servers, 8 tokens: 94 us per step tiled, 96 with both
-// streamed; Zipf 1.2, 16 tokens: 207 and 218).  The down GEMM has 256-row
-// tiles to spread over the chip.  Steps, tiled -> streaming, same run: mixtral
-// shape 1 token 162 -> 86 us, 4 tokens 248 -> 186, 16 tokens 328 -> 296; qwen3
-// shape 42 -> 32, 48 -> 40, 118 -> 105; dsv3 shape 92 -> 88, 203 -> 191,
-// 247 -> 229, with Zipf 1.2 routing 207 -> 199.
-bool stream_act8(const FfnArgs& a, bool gateup) { return a.T <= (gateup ? 4 : 16); }
-
 }  // namespace
 
 hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N, int K, int I,
@@ -1576,17 +1530,7 @@ hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N,
   return hipGetLastError();
 }
 
-bool gate_up_routes(const FfnArgs& a) {
-  const long long R = (long long)a.T * a.k;
-  if (a.ids == nullptr || R > kSelfSlots) return false;
-  if (!a.act8) return stream_shape(a, true) == kStreamFew;
-  // Only where one workgroup per CU covers every slot's columns: the groups
-  // without rows are not compacted away, and with more workgroups than CUs the
-  // ones that have work pile up on some of them (dsv3 shape, 16 tokens with
-  // ids of 8 servers: 167 us, compacted by the routing launch 119, tiled 125;
-  // qwen3 shape, 16 tokens, Zipf 1.2: 59, tiled 51).
-  return stream_act8(a, true) && R <= a.E && R * (2 * a.I / 256) <= 256;
-}
+bool gate_up_routes(const FfnArgs& a) { return a.ids != nullptr && gemm_plan(a, true).routes; }
 
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
   // [R,H] x [2I,H]^T -> h [R,I]
@@ -1610,12 +1554,11 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
     g.counts = a.counts;
     g.inv = a.inv;
   }
-  if (a.act8)
-    return stream_act8(a, true) ? launch_gemm_stream_a8<kGateUp>(g, R, a.E, stream)
-                          : launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
-  const StreamShape shape = stream_shape(a, true);
-  return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, shape, stream)
-               : launch_kind<kGateUp, false>(g, R, a.E, shape, stream);
+  const GemmPath path = gemm_plan(a, true).path;
+  if (path == kPathStreamA8) return launch_gemm_stream_a8<kGateUp>(g, R, a.E, stream);
+  if (path == kPathTiledA8) return launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
+  return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, path, stream)
+               : launch_kind<kGateUp, false>(g, R, a.E, path, stream);
 }
 
 hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
@@ -1630,21 +1573,21 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
   g.y = a.y;
   g.down = true;
   const int R = a.T * a.k;
+  const GemmPath path = gemm_plan(a, false).path;
   if (a.act8) {
     g.a8 = a.hq;
     g.a_scale = a.hs;
-    if (stream_act8(a, false))
+    if (path == kPathStreamA8)
       return a.epilogue == kDownBySlot ? launch_gemm_stream_a8<kDownBySlotK>(g, R, a.E, stream)
                                        : launch_gemm_stream_a8<kDownPlainK>(g, R, a.E, stream);
     return a.epilogue == kDownBySlot ? launch_w8a8<kDownBySlotK>(g, R, a.E, small_rows(a), stream)
                                      : launch_w8a8<kDownPlainK>(g, R, a.E, small_rows(a), stream);
   }
-  const StreamShape shape = stream_shape(a, false);
   if (a.epilogue == kDownBySlot)
-    return a.fp8 ? launch_kind<kDownBySlotK, true>(g, R, a.E, shape, stream)
-                 : launch_kind<kDownBySlotK, false>(g, R, a.E, shape, stream);
-  return a.fp8 ? launch_kind<kDownPlainK, true>(g, R, a.E, shape, stream)
-               : launch_kind<kDownPlainK, false>(g, R, a.E, shape, stream);
+    return a.fp8 ? launch_kind<kDownBySlotK, true>(g, R, a.E, path, stream)
+                 : launch_kind<kDownBySlotK, false>(g, R, a.E, path, stream);
+  return a.fp8 ? launch_kind<kDownPlainK, true>(g, R, a.E, path, stream)
+               : launch_kind<kDownPlainK, false>(g, R, a.E, path, stream);
 }
 
 }  // namespace eaas

@@ -4,7 +4,7 @@
 #pragma once
 
 #include "common.h"
-#include "internal.h"
+#include "dispatch.h"
 
 namespace eaas {
 
@@ -124,15 +124,9 @@ __device__ __forceinline__ const void* wave_uniform(const void* p) {
   return reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo);
 }
 
-// Most slots of a batch whose gate/up launch routes its rows itself.
-constexpr int kSelfSlots = 512;
-
-// The register-streaming kernels (gemm_stream.hip): row blocks of up to 64 rows
-// (one wave or four per workgroup), or of up to 144 rows by 256 or 128 weight
-// rows.
-enum StreamShape { kNotStreamed = 0, kStreamFew = 1, kStreamWide8 = 2, kStreamWide4 = 3 };
+// The register-streaming kernels (gemm_stream.hip) of the given path.
 template <int KIND, bool FP8>
-hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, StreamShape shape,
+hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, GemmPath path,
                               hipStream_t stream);
 // The same for fp8 weights times fp8 activations (row-major weights).
 template <int KIND>

@@ -924,16 +924,12 @@ void grouped_gemm_stream_a8_kernel(GemmParams p) {
 }
 
 template <int KIND, int W>
-hipError_t enqueue(const GemmParams& p, int R, int E, StreamShape shape, hipStream_t stream) {
-  if (shape == kStreamWide8) return launch_shared<KIND, W, Wide8<W>>(p, R, E, stream);
-  if (shape == kStreamWide4) return launch_shared<KIND, W, Wide4<W>>(p, R, E, stream);
+hipError_t enqueue(const GemmParams& p, int R, int E, GemmPath path, hipStream_t stream) {
+  if (path == kPathWide8) return launch_shared<KIND, W, Wide8<W>>(p, R, E, stream);
+  if (path == kPathWide4) return launch_shared<KIND, W, Wide4<W>>(p, R, E, stream);
   const bool self = KIND == kGateUp && p.ids != nullptr;
-  // one wave per workgroup up to two rows per expert on average: with the
-  // waves of 1 to 16 tokens its start-up is shorter (qwen3, 1 token: gate/up
-  // 25 -> 16 us, 16 tokens 108 -> 102); from 2 rows on they are equal, and
-  // past 4 the rows that every wave loads by itself cost more
-  if ((long long)R > 2LL * E && !self) return launch_shared<KIND, W, Few<W>>(p, R, E, stream);
-  const int waves = (long long)R > 2LL * E ? Few<W>::NW : 1;
+  if (path == kPathFew && !self) return launch_shared<KIND, W, Few<W>>(p, R, E, stream);
+  const int waves = path == kPathFew ? Few<W>::NW : 1;
   const long long grid = (long long)std::min(E, R) * (p.N / (32 * waves)) + self;
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -972,24 +968,24 @@ template hipError_t launch_gemm_stream_a8<kDownPlainK>(const GemmParams&, int, i
 template hipError_t launch_gemm_stream_a8<kDownBySlotK>(const GemmParams&, int, int, hipStream_t);
 
 template <int KIND, bool FP8>
-hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, StreamShape shape,
+hipError_t launch_gemm_stream(const GemmParams& p, int R, int E, GemmPath path,
                               hipStream_t stream) {
-  if constexpr (!FP8) return enqueue<KIND, kBf16Rows>(p, R, E, shape, stream);
-  else if (p.tiled) return enqueue<KIND, kFp8Tiled>(p, R, E, shape, stream);
-  else return enqueue<KIND, kFp8Rows>(p, R, E, shape, stream);
+  if constexpr (!FP8) return enqueue<KIND, kBf16Rows>(p, R, E, path, stream);
+  else if (p.tiled) return enqueue<KIND, kFp8Tiled>(p, R, E, path, stream);
+  else return enqueue<KIND, kFp8Rows>(p, R, E, path, stream);
 }
 
-template hipError_t launch_gemm_stream<kGateUp, false>(const GemmParams&, int, int, StreamShape,
+template hipError_t launch_gemm_stream<kGateUp, false>(const GemmParams&, int, int, GemmPath,
     hipStream_t);
-template hipError_t launch_gemm_stream<kGateUp, true>(const GemmParams&, int, int, StreamShape,
+template hipError_t launch_gemm_stream<kGateUp, true>(const GemmParams&, int, int, GemmPath,
     hipStream_t);
-template hipError_t launch_gemm_stream<kDownPlainK, false>(const GemmParams&, int, int, StreamShape,
+template hipError_t launch_gemm_stream<kDownPlainK, false>(const GemmParams&, int, int, GemmPath,
     hipStream_t);
-template hipError_t launch_gemm_stream<kDownPlainK, true>(const GemmParams&, int, int, StreamShape,
+template hipError_t launch_gemm_stream<kDownPlainK, true>(const GemmParams&, int, int, GemmPath,
     hipStream_t);
-template hipError_t launch_gemm_stream<kDownBySlotK, false>(const GemmParams&, int, int, StreamShape,
+template hipError_t launch_gemm_stream<kDownBySlotK, false>(const GemmParams&, int, int, GemmPath,
     hipStream_t);
-template hipError_t launch_gemm_stream<kDownBySlotK, true>(const GemmParams&, int, int, StreamShape,
+template hipError_t launch_gemm_stream<kDownBySlotK, true>(const GemmParams&, int, int, GemmPath,
     hipStream_t);
 
 }  // namespace eaas
