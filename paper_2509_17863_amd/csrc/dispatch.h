@@ -24,6 +24,9 @@ struct GemmPlan {
 
 // Most slots of a batch whose gate/up launch routes its rows itself.
 constexpr int kSelfSlots = 512;
+// Rows that a one-wave workgroup, and a self-routing one of four waves, takes
+// at once; it walks an expert's further rows in series.
+constexpr int kOneWaveRows = 32, kFewRows = 64;
 
 // Which batches the streaming kernels of gemm_stream.hip take, by the slots per
 // resident expert.  A dynamic batch passes its capacity, which it rarely fills
@@ -41,6 +44,18 @@ constexpr int kSelfSlots = 512;
 // of 1 to 16 tokens its start-up is shorter (qwen3, 1 token: gate/up 25 -> 16
 // us, 16 tokens 108 -> 102); from 2 rows on they are equal, and past 4 the rows
 // that every wave loads by itself cost more.
+// The one-wave kernel takes no batch of more than 32 tokens, and a launch routes
+// itself for no more than 64: an expert then has one block of rows (a token's
+// slots name different experts).  Past that a hot expert's blocks follow one
+// another in each workgroup, where the routing launch's row blocks go to
+// different ones (k 1, whole step, tiled / in series / row blocks: H 2048, I
+// 512, E 256, 512 tokens of one expert, bf16: 66 / 196 / 47 us; 512 tokens,
+// Zipf 1.2: 71 / 160 / 50; H 4096, I 2048, E 32, 512 tokens, Zipf 1.2, fp8: 165
+// / 218 / 133).
+// Row blocks are found 64 active experts at a time, about 1 us a step, so a long
+// list needs a long K (whole step, tiled / row blocks: H 1024, I 256, E 1024,
+// k 1, 2048 tokens: fp8 210 / 294 us, bf16 306 / 340; H 4096, I 1024, E 512,
+// k 8, 96 tokens, fp8: 954 / 809).
 // One 144-row block per expert (up to 120 slots, so that random counts stay
 // below 144): the fp8 gate/up GEMM, whose tiled kernel needs a second tile past
 // 96 rows: dsv3 shape 64 slots 209 -> 182 us, 64 with Zipf 1.2 302 -> 264, 96:
@@ -57,10 +72,13 @@ constexpr int kSelfSlots = 512;
 // E 5, k 2, 280 slots: 43 against 32).
 inline GemmPath stream_path(const FfnArgs& a, bool gateup) {
   const long long R = (long long)a.T * a.k, N = gateup ? 2LL * a.I : a.H;
-  if (R <= (a.capacity ? 48 : a.fp8 ? 32 : 24) * (long long)a.E)
-    return R <= 2LL * a.E ? kPathOneWave : kPathFew;
+  const bool few = R <= (a.capacity ? 48 : a.fp8 ? 32 : 24) * (long long)a.E;
+  if (few && R <= 2LL * a.E && a.T <= kOneWaveRows) return kPathOneWave;
+  const long long steps = ((R < a.E ? R : a.E) + 63) / 64;
+  const bool short_k = (gateup ? a.H : a.I) < 128 * (steps - 1);
+  if (few && !short_k) return kPathFew;
   if (N % 256 && (R <= 350LL * a.E || (R / 144 + a.E) * (N / 128) <= 512)) return kPathWide4;
-  if (R > (a.capacity ? 480 : 120) * (long long)a.E) return kPathTiled;
+  if (R > (a.capacity ? 480 : 120) * (long long)a.E || short_k) return kPathTiled;
   if (a.E * (N / 128) <= 256) return kPathWide4;
   return a.fp8 && gateup ? kPathWide8 : kPathTiled;
 }
@@ -79,7 +97,8 @@ inline GemmPlan gemm_plan(const FfnArgs& a, bool gateup) {
   const long long R = (long long)a.T * a.k;
   if (!a.act8) {
     const GemmPath path = stream_path(a, gateup);
-    return {path, gateup && R <= kSelfSlots && (path == kPathOneWave || path == kPathFew)};
+    return {path, gateup && R <= kSelfSlots && a.T <= kFewRows &&
+                      (path == kPathOneWave || path == kPathFew)};
   }
   const bool stream = a.T <= (gateup ? 4 : 16);
   // Routing inside the launch only where one workgroup per CU covers every

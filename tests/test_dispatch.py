@@ -25,6 +25,33 @@ def test_paths(T, shape, wdt, gate_up, expect):
     assert path(T, shape, wdt, gate_up) == expect
 
 
+@pytest.mark.parametrize("wdt", [BF16, FP8, eaas.EAAS_FP8_E4M3_TILED])
+@pytest.mark.parametrize("capacity", [False, True])
+def test_a_hot_expert_is_not_walked_in_series(wdt, capacity):
+    """The kernels that walk an expert's rows block by block in one workgroup
+    (one wave: 32 rows, self-routing: 64) get no batch of more tokens than one
+    block holds: with distinct ids per token no expert has more rows."""
+    for E in (1, 2, 16, 32, 128, 256, 1024):
+        for k in (1, 2, 4, 8, 64):
+            for T in (1, 16, 32, 33, 64, 65, 128, 512, 2048):
+                for gate_up in (True, False):
+                    p, routes = eaas._gemm_plan(T, 512, 256, E, k, wdt, gate_up, capacity)
+                    assert p != "one_wave" or T <= 32, (T, E, k)
+                    assert not routes or T <= 64, (T, E, k)
+    assert eaas._gemm_plan(32, 2048, 512, 256, 8, wdt, True, capacity) == ("one_wave", True)
+    assert eaas._gemm_plan(64, 2048, 512, 32, 8, wdt, True, capacity) == ("few", True)
+
+
+def test_a_long_list_of_experts_needs_a_long_k():
+    """Row blocks are found 64 active experts at a time, in series."""
+    assert path(2048, (1024, 256, 1024, 1), FP8) == "tiled"
+    assert path(2048, (4096, 256, 1024, 1), FP8) == "few"
+    assert path(512, (4096, 1024, 512, 8), FP8, False) == "few"
+    assert path(128, (1024, 256, 1024, 1), FP8) == "few"      # at most 128 active
+    assert path(256, QWEN3, BF16, False) == "few"             # K 768, 128 experts
+    assert path(64, (256, 128, 8, 2), BF16, False) == "few"   # K 128, 8 experts
+
+
 def test_rejected_shapes_have_no_plan():
     for H, wdt in ((100, BF16), (384, A8), (384, eaas.EAAS_FP8_E4M3_TILED)):
         with pytest.raises(eaas.EaasError):

@@ -83,6 +83,42 @@ def test_row_counts_and_k_lengths(gpu, rows, wdtype, H, I):
     assert float(np.abs(got - ref).max()) <= TOL * rms
 
 
+@pytest.mark.parametrize("T,k,E,counts", [
+    (32, 4, 64, [34, 33, 32, 17] + [1] * 12),                   # one wave, 32 rows at a time
+    (64, 8, 32, [130, 65, 64, 63, 17, 16, 129, 1] + [3] * 9),   # self-routing, 64 at a time
+    (65, 8, 33, [130, 65, 64, 63, 17, 16, 129, 1] + [5] * 7)])  # one token more: row blocks
+@pytest.mark.parametrize("wdtype", ["bf16", "fp8"])
+def test_repeated_ids_fill_several_row_blocks(gpu, T, k, E, counts, wdtype):
+    """A token may name an expert more than once, so an expert of a small batch
+    can have more rows than one block: the whole step and the separate entry
+    points (which never route inside the GEMM), against the oracle."""
+    print(f"repeated ids T={T} k={k} E={E} {wdtype}", flush=True)
+    H, I = 384, 128
+    rng = np.random.default_rng(T + E)
+    ids = np.full(T * k, -1, np.int32)
+    slots = rng.permutation(np.repeat(np.arange(len(counts)), counts))
+    ids[: len(slots)] = slots
+    d = synth.make_inputs(T, H, I, E, min(k, E), 79, wdtype=wdtype)
+    d.update(k=k, topk_ids=rng.permutation(ids).reshape(T, k).astype(np.int32),
+             topk_weights=rng.uniform(0.2, 1.0, (T, k)).astype(np.float32))
+    dev = to_device(d)
+    wdt = eaas.EAAS_BF16 if wdtype == "bf16" else eaas.EAAS_FP8_E4M3
+    got = run(dev, k, wdt)
+    ref = O.expert_forward(d)["out"]
+    rms = float(np.sqrt((ref ** 2).mean()))
+    assert float(np.abs(got - ref).max()) <= TOL * rms
+    r = eaas.alloc_routing(T, k, E)
+    ws = eaas.alloc_workspace(T, H, I, E, k, wdt)
+    y = torch.zeros((T * k, H), dtype=torch.float32, device="cuda")
+    out = torch.empty((T, H), dtype=torch.float32, device="cuda")
+    eaas.eaas_route_permute(dev["topk_ids"], E, r, ws, H=H, I=I)
+    eaas.eaas_expert_ffn_grouped(dev["x"], r, dev["w_gate_up"], dev["w_down"], y, ws, k,
+                                 dev["w_gate_up_scale"], dev["w_down_scale"])
+    eaas.eaas_unpermute_combine(y, r, dev["topk_weights"], out, E, I=I)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), got.view(np.uint32))
+
+
 @pytest.mark.parametrize("T,k,E", [(1, 8, 32), (1, 1, 1), (2, 8, 1024), (64, 8, 128), (63, 5, 24),
                                    (64, 8, 32), (4, 8, 33), (128, 4, 65), (512, 1, 512), (3, 2, 2),
                                    (100, 5, 21), (65, 8, 30)])
