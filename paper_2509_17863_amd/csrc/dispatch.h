@@ -97,8 +97,18 @@ inline GemmPlan gemm_plan(const FfnArgs& a, bool gateup) {
   const long long R = (long long)a.T * a.k;
   if (!a.act8) {
     const GemmPath path = stream_path(a, gateup);
+    // Routing inside the launch saves the routing launch (3 to 5 us), but groups
+    // without rows are not compacted away, and where four-wave workgroups are
+    // more than the chip holds at once (two on each CU) those that have work
+    // pile up on some CUs (whole step, routed by a launch / inside: dsv3 shape
+    // bf16, 16 tokens with ids of 8 servers, Zipf 1.2, 4 096 waves: 112 / 158 us;
+    // H 2048, I 768, E 256, k 8, 48 equal tokens, 12 288 waves: 49 / 60).
+    // One-wave workgroups are short enough to even out on most batches (4 096
+    // waves, dsv3 shape, 4 tokens: 158 / 156, Zipf 1.2: 137 / 132, ids of 8
+    // servers: 49 / 54; qwen3 shape bf16, 8 tokens, 3 072 waves: 104 / 92).
+    const long long waves = (R < a.E ? R : a.E) * (2 * a.I / 32);
     return {path, gateup && R <= kSelfSlots && a.T <= kFewRows &&
-                      (path == kPathOneWave || path == kPathFew)};
+                      (path == kPathOneWave || (path == kPathFew && waves <= 2048))};
   }
   const bool stream = a.T <= (gateup ? 4 : 16);
   // Routing inside the launch only where one workgroup per CU covers every

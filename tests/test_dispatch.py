@@ -38,8 +38,25 @@ def test_a_hot_expert_is_not_walked_in_series(wdt, capacity):
                     p, routes = eaas._gemm_plan(T, 512, 256, E, k, wdt, gate_up, capacity)
                     assert p != "one_wave" or T <= 32, (T, E, k)
                     assert not routes or T <= 64, (T, E, k)
-    assert eaas._gemm_plan(32, 2048, 512, 256, 8, wdt, True, capacity) == ("one_wave", True)
+    assert eaas._gemm_plan(32, 2048, 128, 256, 8, wdt, True, capacity) == ("one_wave", True)
     assert eaas._gemm_plan(64, 2048, 512, 32, 8, wdt, True, capacity) == ("few", True)
+
+
+@pytest.mark.parametrize("wdt", [BF16, FP8, eaas.EAAS_FP8_E4M3_TILED])
+def test_self_routing_grids_fit_the_chip(wdt):
+    """Groups without rows are not compacted away by a launch that routes
+    itself: four-wave workgroups are then at most what the chip holds at once
+    (two on each of 256 CUs), so that those with rows cannot pile up."""
+    for E in (1, 8, 24, 32, 64, 128, 256, 1024):
+        for k in (1, 2, 6, 8):
+            for I in (128, 640, 768, 2048, 14336):
+                for T in (1, 2, 3, 4, 8, 16, 17, 32, 33, 64):
+                    p, routes = eaas._gemm_plan(T, 1024, I, E, k, wdt, True)
+                    waves = min(E, T * k) * 2 * I // 32
+                    assert not (routes and p == "few") or waves <= 2048, (T, E, k, I)
+    assert eaas._gemm_plan(16, 1024, 1024, 32, 8, wdt, True) == ("few", True)  # 2 048 waves
+    assert eaas._gemm_plan(16, *DSV3, wdt, True) == ("few", False)             # 4 096
+    assert eaas._gemm_plan(8, *DSV3, wdt, True) == ("one_wave", True)
 
 
 def test_a_long_list_of_experts_needs_a_long_k():

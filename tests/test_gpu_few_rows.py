@@ -121,12 +121,13 @@ def test_repeated_ids_fill_several_row_blocks(gpu, T, k, E, counts, wdtype):
 
 @pytest.mark.parametrize("T,k,E", [(1, 8, 32), (1, 1, 1), (2, 8, 1024), (64, 8, 128), (63, 5, 24),
                                    (64, 8, 32), (4, 8, 33), (128, 4, 65), (512, 1, 512), (3, 2, 2),
-                                   (100, 5, 21), (65, 8, 30)])
+                                   (100, 5, 21), (65, 8, 30), (32, 16, 256), (8, 64, 256)])
 @pytest.mark.parametrize("wdtype", ["bf16", "fp8"])
 def test_routing_of_small_batches(gpu, T, k, E, wdtype):
-    """Up to 512 slots the gate/up launch routes the rows itself: the routing
-    arrays it writes (and the step's output) against the oracle, with masked
-    and repeated ids.  (65 x 8 slots take the routing launch.)"""
+    """Up to 512 slots of up to 64 tokens the gate/up launch routes the rows
+    itself: the routing arrays it writes (and the step's output) against the
+    oracle, with masked and repeated ids.  (More tokens or slots take the
+    routing launch.)"""
     print(f"small-batch routing T={T} k={k} E={E} {wdtype}", flush=True)
     H, I, R = 128, 128, T * k
     d = synth.make_inputs(T, H, I, E, min(k, E), 5 * T + E, wdtype=wdtype)
