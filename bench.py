@@ -57,7 +57,11 @@ def gate_up_kernel_name(d: dict) -> str:
     fp8 = d["wdtype"] == "fp8"
     wdt = eaas.EAAS_BF16 if not fp8 else \
         eaas.EAAS_FP8_E4M3_A8 if d.get("act8") else eaas.EAAS_FP8_E4M3
-    path, _ = eaas._gemm_plan(d["T"], d["H"], d["I"], d["E"], d["k"], wdt, True)
+    counts = None
+    if "topk_ids" in d:
+        ids = np.asarray(d["topk_ids"]).ravel()
+        counts = np.bincount(ids[(ids >= 0) & (ids < d["E"])], minlength=d["E"])
+    path = eaas._gemm_plan(d["T"], d["H"], d["I"], d["E"], d["k"], wdt, True, counts=counts)[0]
     return {"tiled": "grouped_gemm_dma_kernel<gate/up, fp8 weights>" if fp8
             else "grouped_gemm_pp_kernel<gate/up>",
             "one_wave": f"grouped_gemm_stream_kernel<gate/up, {d['wdtype']}>",

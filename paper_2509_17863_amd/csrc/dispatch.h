@@ -19,7 +19,8 @@ enum GemmPath {
 
 struct GemmPlan {
   GemmPath path;
-  bool routes;  // gate/up: the launch routes the batch itself if it has the ids
+  bool routes;   // gate/up: the launch routes the batch itself if it has the ids
+  RowRule rule;  // between this path and the tiled kernels
 };
 
 // Most slots of a batch whose gate/up launch routes its rows itself.
@@ -27,10 +28,14 @@ constexpr int kSelfSlots = 512;
 // Rows that a one-wave workgroup, and a self-routing one of four waves, takes
 // at once; it walks an expert's further rows in series.
 constexpr int kOneWaveRows = 32, kFewRows = 64;
+// Rows of the tallest streamed block.
+constexpr int kWideRows = 144;
 
-// Which batches the streaming kernels of gemm_stream.hip take, by the slots per
-// resident expert.  A dynamic batch passes its capacity, which it rarely fills
-// (and slots of other servers' experts count too), so its limits are higher.
+// Which batches the streaming kernels of gemm_stream.hip may take, by the slots
+// per resident expert.  The host knows the slots, which other servers' experts
+// and (dynamic batches pass their capacity) unused room share, but not the rows
+// of each expert; where the answer hangs on those, row_rule below lets the
+// device choose.
 //
 // Few rows: step times, tiled kernels -> streaming (us), by slots per expert:
 //   bf16: qwen3 shape 2: 226 -> 190, 32: 284 -> 261, 48: 298 -> 289, 64: 312 ->
@@ -56,8 +61,7 @@ constexpr int kOneWaveRows = 32, kFewRows = 64;
 // list needs a long K (whole step, tiled / row blocks: H 1024, I 256, E 1024,
 // k 1, 2048 tokens: fp8 210 / 294 us, bf16 306 / 340; H 4096, I 1024, E 512,
 // k 8, 96 tokens, fp8: 954 / 809).
-// One 144-row block per expert (up to 120 slots, so that random counts stay
-// below 144): the fp8 gate/up GEMM, whose tiled kernel needs a second tile past
+// One 144-row block per expert: the fp8 gate/up GEMM, whose tiled kernel needs a second tile past
 // 96 rows: dsv3 shape 64 slots 209 -> 182 us, 64 with Zipf 1.2 302 -> 264, 96:
 // 327 -> 239; at 128 it is 336 -> 355.  (The down GEMM's smaller tiled
 // workgroups are as fast: 64: 132 -> 129, 96: 163 -> 159.)
@@ -78,9 +82,40 @@ inline GemmPath stream_path(const FfnArgs& a, bool gateup) {
   const bool short_k = (gateup ? a.H : a.I) < 128 * (steps - 1);
   if (few && !short_k) return kPathFew;
   if (N % 256 && (R <= 350LL * a.E || (R / 144 + a.E) * (N / 128) <= 512)) return kPathWide4;
-  if (R > (a.capacity ? 480 : 120) * (long long)a.E || short_k) return kPathTiled;
+  if (R > (a.capacity ? 1024 : 120) * (long long)a.E || short_k) return kPathTiled;
   if (a.E * (N / 128) <= 256) return kPathWide4;
   return a.fp8 && gateup ? kPathWide8 : kPathTiled;
+}
+
+// When the rows decide.  (Times of one GEMM, tiled -> streamed, in us.)
+//   64-row blocks: up to 64 tokens an expert has one block, and up to 256 tokens
+//     and 16 slots per expert further blocks cost about what the choice does.
+//     Past that each block re-reads its weights: qwen3 shape bf16, gate/up, 512
+//     tokens, even (one block an expert) 185 -> 157, Zipf 1.2 (124 blocks of 77
+//     experts) 122 -> 130, 384 equal tokens (48 blocks of 8) 51 -> 66.  fp8 has
+//     96-row tiles to beat: dsv3 shape, 192 tokens, Zipf 1.2 (45 of 32) 275 ->
+//     219.  With many rows a block the tiled MFMAs win: the same, 48 rows per
+//     expert, even, 171 -> 175.  Blocks that fill the chip once win all the same:
+//     mixtral shape fp8, down, 128 equal tokens (4 blocks of 2) 190 -> 110.
+//   144-row blocks, eight waves: an expert's second block is a second pass over
+//     its weights: dsv3 shape fp8, gate/up, 384 tokens, even 301 -> 221, Zipf 0.8
+//     (39 of 32) 289 -> 323, 960 tokens (64 of 32) 473 -> 504.
+//   144-row blocks, four waves: one workgroup per CU, so a second round doubles
+//     the time: mixtral shape bf16, down, 480 tokens (256 workgroups) 276 -> 211,
+//     320 with Zipf 0.8 (288) 278 -> 348, 960 (512) 323 -> 374.
+// The launch that is not chosen costs 2 to 3 us.
+inline RowRule row_rule(const FfnArgs& a, bool gateup, GemmPath path) {
+  const long long R = (long long)a.T * a.k;
+  const int N = gateup ? 2 * a.I : a.H;
+  if (N % 256) return {0, 0, 0, 0};
+  RowRule r{0, 0, 0, 0};
+  if (path == kPathFew && a.T > kFewRows && (a.T > 256 || R > 16LL * a.E))
+    r = a.fp8 ? RowRule{kFewRows, 512 / (N / 128), 3, 40} : RowRule{kFewRows, 256 / (N / 128), 4, 32};
+  if (path == kPathWide8 && a.T > kWideRows) r = {kWideRows, 256 / (N / 256), 5, kWideRows};
+  if (path == kPathWide4 && a.T > kWideRows) r = {kWideRows, 256 / (N / 128), 0, 0};
+  // no routing of these slots has more blocks than the chip holds
+  if (r.height > 0 && R / r.height + a.E <= r.one_round) r.height = 0;
+  return r;
 }
 
 // fp8 activations: the streaming kernel takes the gate/up GEMM of up to 4
@@ -108,7 +143,8 @@ inline GemmPlan gemm_plan(const FfnArgs& a, bool gateup) {
     // servers: 49 / 54; qwen3 shape bf16, 8 tokens, 3 072 waves: 104 / 92).
     const long long waves = (R < a.E ? R : a.E) * (2 * a.I / 32);
     return {path, gateup && R <= kSelfSlots && a.T <= kFewRows &&
-                      (path == kPathOneWave || (path == kPathFew && waves <= 2048))};
+                      (path == kPathOneWave || (path == kPathFew && waves <= 2048)),
+            row_rule(a, gateup, path)};
   }
   const bool stream = a.T <= (gateup ? 4 : 16);
   // Routing inside the launch only where one workgroup per CU covers every
@@ -118,7 +154,8 @@ inline GemmPlan gemm_plan(const FfnArgs& a, bool gateup) {
   // routing launch 119, tiled 125; qwen3 shape, 16 tokens, Zipf 1.2: 59, tiled
   // 51).
   return {stream ? kPathStreamA8 : kPathTiledA8,
-          gateup && stream && R <= kSelfSlots && R <= a.E && R * (2 * a.I / 256) <= 256};
+          gateup && stream && R <= kSelfSlots && R <= a.E && R * (2 * a.I / 256) <= 256,
+          RowRule{0, 0, 0, 0}};
 }
 
 }  // namespace eaas

@@ -131,10 +131,12 @@ hipError_t before_gate_up(FfnArgs& a, const int32_t* ids, const eaas_routing& rt
   a.ids = ids;
   a.counts = rt.counts;
   a.inv = rt.inv;
+  int32_t* hist = reinterpret_cast<int32_t*>(base + L.hist);
+  const RowChoice choice = row_choice(a, hist);
+  a.choice = choice.word;
   hipError_t e = hipSuccess;
-  if (!gate_up_routes(a))
-    e = launch_route_permute(ids, a.T * a.k, a.E, rt, reinterpret_cast<int32_t*>(base + L.hist),
-                             hs);
+  if (!gate_up_routes(a)) e = launch_route_permute(ids, a.T * a.k, a.E, rt, hist, choice, hs);
+  else if (choice.word) return hipErrorInvalidValue;  // (a batch that routes itself has no choice)
   return e == hipSuccess ? quantize_x(a, base, L, hs) : e;
 }
 
@@ -241,7 +243,7 @@ int eaas_route_permute(const eaas_shape* s, const int32_t* topk_ids, const eaas_
   if (!ws || !aligned16(ws) || ws_bytes < L.route_total) return EAAS_ERR_WORKSPACE;
   char* base = static_cast<char*>(ws);
   return hip_status(launch_route_permute(topk_ids, s->T * s->k, s->E, *r,
-                                         reinterpret_cast<int32_t*>(base + L.hist),
+                                         reinterpret_cast<int32_t*>(base + L.hist), RowChoice{},
                                          reinterpret_cast<hipStream_t>(stream)));
 }
 
@@ -274,7 +276,10 @@ int eaas_expert_ffn_grouped(const eaas_shape* s, const void* x, const eaas_routi
   a.y = y_perm;
   a.epilogue = kDownPlain;
   hipStream_t hs = reinterpret_cast<hipStream_t>(stream);
-  hipError_t e = quantize_x(a, base, L, hs);
+  const RowChoice choice = row_choice(a, reinterpret_cast<int32_t*>(base + L.hist));
+  a.choice = choice.word;
+  hipError_t e = launch_row_choice(r->offsets, s->T * s->k, s->E, choice, hs);
+  if (e == hipSuccess) e = quantize_x(a, base, L, hs);
   if (e == hipSuccess) e = launch_gate_up(a, hs);
   if (e == hipSuccess) e = launch_down(a, hs);
   return hip_status(e);
@@ -567,8 +572,11 @@ int eaas_expert_forward_noalloc(const eaas_shape* s, const void* x, const int32_
 
 // Not part of the ABI: the kernels a batch takes, for tests and measurements.
 // Returns the GemmPath of the GEMM plus 16 if its launch also routes the batch
-// (entry points that take ids), or -1 for what the library rejects.
-int eaas_internal_gemm_plan(const eaas_shape* s, int w_dtype, int capacity, int gate_up) {
+// (entry points that take ids) and 32 if the rows decide between that path and
+// the tiled kernels; or -1 for what the library rejects.  counts (optional,
+// host): rows of each of the E experts, for which the choice is made.
+int eaas_internal_gemm_plan(const eaas_shape* s, int w_dtype, int capacity, int gate_up,
+                            const int32_t* counts) {
   if (check_shape(s) != EAAS_OK || !known_wdtype(w_dtype) ||
       check_dtype_shape(s, w_dtype) != EAAS_OK)
     return -1;
@@ -578,7 +586,18 @@ int eaas_internal_gemm_plan(const eaas_shape* s, int w_dtype, int capacity, int 
   a.act8 = w_dtype == EAAS_FP8_E4M3_A8;
   a.capacity = capacity != 0;
   const GemmPlan plan = gemm_plan(a, gate_up != 0);
-  return (int)plan.path + (plan.routes ? 16 : 0);
+  const bool rule = plan.rule.height > 0;
+  int path = plan.path;
+  if (counts && rule) {
+    int active = 0, blocks = 0, rows = 0;
+    for (int e = 0; e < a.E; ++e) {
+      active += counts[e] > 0;
+      blocks += (counts[e] + plan.rule.height - 1) / plan.rule.height;
+      rows += counts[e];
+    }
+    if (!rows_stream(plan.rule, active, blocks, rows)) path = kPathTiled;
+  }
+  return path + (plan.routes ? 16 : 0) + (rule ? 32 : 0);
 }
 
 const char* eaas_status_string(int status) {

@@ -677,7 +677,7 @@ void grouped_gemm_dma_kernel(GemmParams p) {
   {
     int* s_tp = reinterpret_cast<int*>(smem_raw);
     int* s_exp = s_tp + kMaxExperts + 1;
-    if (!locate_tile<BM, BN, NT>(p, s_tp, s_exp, s_wave, t)) return;
+    if (not_this_launch(p) || !locate_tile<BM, BN, NT>(p, s_tp, s_exp, s_wave, t)) return;
     __syncthreads();  // every lane has its tile before the DMA overwrites the tables
   }
 
@@ -849,7 +849,7 @@ void grouped_gemm_pp_kernel(GemmParams p) {
     int* s_tp = reinterpret_cast<int*>(smem_raw);
     int* s_exp = s_tp + kMaxExperts + 1;
     int* s_wave = s_exp + kMaxExperts + 1;
-    if (!locate_tile<BM, BN, NT>(p, s_tp, s_exp, s_wave, t)) return;
+    if (not_this_launch(p) || !locate_tile<BM, BN, NT>(p, s_tp, s_exp, s_wave, t)) return;
     __syncthreads();  // every lane has its tile before the DMA overwrites the tables
   }
 
@@ -1481,8 +1481,7 @@ __global__ __launch_bounds__(256) void tile_weights_fp8_kernel(const uint8_t* __
 // They cover N / 256 whole tiles; of an N that is no multiple of 256 the last
 // 128 rows go to the streaming kernel.
 template <int KIND, bool FP8>
-hipError_t launch_kind(GemmParams p, int R, int E, GemmPath path, hipStream_t stream) {
-  if (path != kPathTiled) return launch_gemm_stream<KIND, FP8>(p, R, E, path, stream);
+hipError_t launch_tiled(GemmParams p, int R, int E, hipStream_t stream) {
   hipError_t e;
   if constexpr (!FP8)
     e = launch_pp<KIND>(p, R, E, stream);
@@ -1495,6 +1494,21 @@ hipError_t launch_kind(GemmParams p, int R, int E, GemmPath path, hipStream_t st
   if (e != hipSuccess || p.N % 256 == 0) return e;
   p.tn0 = p.N / 256 * 2;
   return launch_gemm_stream<KIND, FP8>(p, R, E, kPathWide4, stream);
+}
+
+template <int KIND, bool FP8>
+hipError_t launch_kind(GemmParams p, int R, int E, const GemmPlan& plan, const int32_t* choice,
+                       hipStream_t stream) {
+  if (plan.path == kPathTiled) return launch_tiled<KIND, FP8>(p, R, E, stream);
+  if (plan.rule.height > 0) {
+    if (choice == nullptr) return hipErrorInvalidValue;
+    p.choice = choice;
+    p.choice_bit = KIND == kGateUp ? 1 : 2;
+  }
+  const hipError_t e = launch_gemm_stream<KIND, FP8>(p, R, E, plan.path, stream);
+  if (e != hipSuccess || p.choice == nullptr) return e;
+  p.tiled_launch = true;
+  return launch_tiled<KIND, FP8>(p, R, E, stream);
 }
 
 GemmParams common_params(const FfnArgs& a) {
@@ -1532,6 +1546,12 @@ hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N,
 
 bool gate_up_routes(const FfnArgs& a) { return a.ids != nullptr && gemm_plan(a, true).routes; }
 
+RowChoice row_choice(const FfnArgs& a, int32_t* word) {
+  RowChoice c{gemm_plan(a, true).rule, gemm_plan(a, false).rule, nullptr};
+  if (c.gate_up.height > 0 || c.down.height > 0) c.word = word;
+  return c;
+}
+
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
   // [R,H] x [2I,H]^T -> h [R,I]
   GemmParams g = common_params(a);
@@ -1554,11 +1574,11 @@ hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream) {
     g.counts = a.counts;
     g.inv = a.inv;
   }
-  const GemmPath path = gemm_plan(a, true).path;
-  if (path == kPathStreamA8) return launch_gemm_stream_a8<kGateUp>(g, R, a.E, stream);
-  if (path == kPathTiledA8) return launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
-  return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, path, stream)
-               : launch_kind<kGateUp, false>(g, R, a.E, path, stream);
+  const GemmPlan plan = gemm_plan(a, true);
+  if (plan.path == kPathStreamA8) return launch_gemm_stream_a8<kGateUp>(g, R, a.E, stream);
+  if (plan.path == kPathTiledA8) return launch_w8a8<kGateUp>(g, R, a.E, small_rows(a), stream);
+  return a.fp8 ? launch_kind<kGateUp, true>(g, R, a.E, plan, a.choice, stream)
+               : launch_kind<kGateUp, false>(g, R, a.E, plan, a.choice, stream);
 }
 
 hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
@@ -1573,21 +1593,21 @@ hipError_t launch_down(const FfnArgs& a, hipStream_t stream) {
   g.y = a.y;
   g.down = true;
   const int R = a.T * a.k;
-  const GemmPath path = gemm_plan(a, false).path;
+  const GemmPlan plan = gemm_plan(a, false);
   if (a.act8) {
     g.a8 = a.hq;
     g.a_scale = a.hs;
-    if (path == kPathStreamA8)
+    if (plan.path == kPathStreamA8)
       return a.epilogue == kDownBySlot ? launch_gemm_stream_a8<kDownBySlotK>(g, R, a.E, stream)
                                        : launch_gemm_stream_a8<kDownPlainK>(g, R, a.E, stream);
     return a.epilogue == kDownBySlot ? launch_w8a8<kDownBySlotK>(g, R, a.E, small_rows(a), stream)
                                      : launch_w8a8<kDownPlainK>(g, R, a.E, small_rows(a), stream);
   }
   if (a.epilogue == kDownBySlot)
-    return a.fp8 ? launch_kind<kDownBySlotK, true>(g, R, a.E, path, stream)
-                 : launch_kind<kDownBySlotK, false>(g, R, a.E, path, stream);
-  return a.fp8 ? launch_kind<kDownPlainK, true>(g, R, a.E, path, stream)
-               : launch_kind<kDownPlainK, false>(g, R, a.E, path, stream);
+    return a.fp8 ? launch_kind<kDownBySlotK, true>(g, R, a.E, plan, a.choice, stream)
+                 : launch_kind<kDownBySlotK, false>(g, R, a.E, plan, a.choice, stream);
+  return a.fp8 ? launch_kind<kDownPlainK, true>(g, R, a.E, plan, a.choice, stream)
+               : launch_kind<kDownPlainK, false>(g, R, a.E, plan, a.choice, stream);
 }
 
 }  // namespace eaas

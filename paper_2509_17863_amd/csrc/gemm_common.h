@@ -53,7 +53,18 @@ struct GemmParams {
   const int32_t* ids;
   int32_t* counts;
   int32_t* inv;
+  // one of two launches of which the batch's rows let one run: where the choice
+  // stands, this GEMM's bit in it, and whether this is the tiled launch
+  const int32_t* choice;
+  int choice_bit;
+  bool tiled_launch;
 };
+
+// Whether the batch is the other launch's.
+__device__ __forceinline__ bool not_this_launch(const GemmParams& p) {
+  if (p.choice == nullptr) return false;
+  return ((*(const CONST_AS int32_t*)p.choice & p.choice_bit) != 0) == p.tiled_launch;
+}
 
 // Weights of group e ([N, K], bf16 or fp8 bytes of esz each).
 __device__ __forceinline__ const uint8_t* group_weights(const GemmParams& p, int e, int esz) {

@@ -825,6 +825,7 @@ __global__ __launch_bounds__(kWave * G::NW) __attribute__((amdgpu_waves_per_eu(G
 void grouped_gemm_shared_kernel(GemmParams p) {
   constexpr int ROWS = 16 * G::MBX;
   __shared__ __attribute__((aligned(16))) char smem[2 * ROWS * (kChunk + 16)];
+  if (not_this_launch(p)) return;
   RowBlock b;
   const int tile = xcd_window_remap(blockIdx.x, gridDim.x);
   if (!locate_rows<ROWS>(p, tile, p.N / (32 * G::NW) - p.tn0, b)) return;

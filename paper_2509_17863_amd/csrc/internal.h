@@ -17,10 +17,35 @@ constexpr int kMaxSegments = 1024;
 
 inline int route_blocks(int R) { return (R + kRouteChunk - 1) / kRouteChunk; }
 
-// Enqueue the three routing kernels.  `hist` holds route_blocks(R) * E ints.
+// Streaming or tiled by the rows that a batch has: both kernels are enqueued,
+// the routing writes which one is to run, and the other's workgroups end at
+// once.  The batch streams if its row blocks fill the chip no more than once, or
+// if few experts have more than one block and few rows each.
+struct RowRule {
+  int height;     // rows of a block; 0: no choice, one kernel alone
+  int one_round;  // blocks that fill the chip once
+  int spare;      // further blocks: one in `spare` active experts
+  int mean;       // rows per active expert, on average
+};
+__host__ __device__ inline bool rows_stream(const RowRule& r, int active, int blocks, int rows) {
+  return blocks <= r.one_round ||
+         ((blocks - active) * r.spare <= active && rows <= r.mean * active);
+}
+// The rules of a batch's two GEMMs and where the choice is written: bit 0 if the
+// gate/up GEMM streams, bit 1 if the down GEMM does.
+struct RowChoice {
+  RowRule gate_up, down;
+  int32_t* word;  // nullptr: no choice to make
+};
+
+// Enqueue the routing.  `hist` holds route_blocks(R) * E ints; the choice's word
+// may be the first of them.
 hipError_t launch_route_permute(const int32_t* ids, int R, int E,
-                                const eaas_routing& r, int32_t* hist,
+                                const eaas_routing& r, int32_t* hist, const RowChoice& choice,
                                 hipStream_t stream);
+// The choice alone, for a routing that is already there.
+hipError_t launch_row_choice(const int32_t* offsets, int R, int E, const RowChoice& choice,
+                             hipStream_t stream);
 
 // Which epilogue the down projection uses.
 enum DownEpilogue {
@@ -60,6 +85,8 @@ struct FfnArgs {
   const int32_t* ids = nullptr;
   int32_t* counts = nullptr;
   int32_t* inv = nullptr;
+  // where the routing wrote the choice between streaming and tiled kernels
+  const int32_t* choice = nullptr;
   // T is the capacity of a dynamic batch: the batch itself is usually smaller
   bool capacity = false;
 };
@@ -79,6 +106,9 @@ hipError_t launch_tile_weights_fp8(const uint8_t* w, uint8_t* out, int E, int N,
 // Whether launch_gate_up routes the batch itself (a.ids given, a small decode
 // batch) and writes all routing arrays, so that no routing launch is needed.
 bool gate_up_routes(const FfnArgs& a);
+// The rules by which the rows choose the kernels of this batch's GEMMs; `word`
+// becomes RowChoice::word if there are any.
+RowChoice row_choice(const FfnArgs& a, int32_t* word);
 // Gate/up GEMM with the SiLU*mul epilogue into h.
 hipError_t launch_gate_up(const FfnArgs& a, hipStream_t stream);
 // Down GEMM from h into y (epilogue per a.epilogue).

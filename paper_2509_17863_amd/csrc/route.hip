@@ -72,10 +72,49 @@ __device__ int block_exclusive_scan_1024(int v, int* s_wave, int* total) {
   return res;
 }
 
+// Which kernels the batch's rows choose: thread e holds expert e's rows (c),
+// blocks[2] is LDS.  Two barriers; thread 0 writes the word.
+__device__ void write_row_choice(const RowChoice& ch, int c, int n_active, int rows, int* blocks) {
+  if (threadIdx.x < 2) blocks[threadIdx.x] = 0;
+  __syncthreads();
+  const int h0 = max(ch.gate_up.height, 1), h1 = max(ch.down.height, 1);
+  int b0 = (c + h0 - 1) / h0, b1 = (c + h1 - 1) / h1;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    b0 += __shfl_xor(b0, d);
+    b1 += __shfl_xor(b1, d);
+  }
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    atomicAdd(&blocks[0], b0);
+    atomicAdd(&blocks[1], b1);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *ch.word = (rows_stream(ch.gate_up, n_active, blocks[0], rows) ? 1 : 0) |
+               (rows_stream(ch.down, n_active, blocks[1], rows) ? 2 : 0);
+}
+
+__global__ __launch_bounds__(kScanThreads) void row_choice_kernel(
+    const int32_t* __restrict__ offsets, int R, int E, RowChoice choice) {
+  __shared__ int s_wave[kScanThreads / kWave + 1];
+  __shared__ int s_blocks[2];
+  const int e = threadIdx.x;  // E <= 1024 = blockDim
+  int c = 0;
+  if (e < E) {
+    // routing arrays may come from the caller
+    const int beg = min(max(offsets[e], 0), R);
+    c = min(max(offsets[e + 1], beg), R) - beg;
+  }
+  int n_active;
+  block_exclusive_scan_1024(c > 0 ? 1 : 0, s_wave, &n_active);
+  write_row_choice(choice, c, n_active, min(max(offsets[E], 0), R), s_blocks);
+}
+
 __global__ __launch_bounds__(kScanThreads) void route_scan_kernel(
     int32_t* __restrict__ hist, int nblk, int E, int32_t* __restrict__ counts,
-    int32_t* __restrict__ offsets, int32_t* __restrict__ active) {
+    int32_t* __restrict__ offsets, int32_t* __restrict__ active, RowChoice choice) {
   __shared__ int s_wave[kScanThreads / kWave + 1];
+  __shared__ int s_blocks[2];
   __shared__ int s_act[kMaxExperts];
   const int e = threadIdx.x;  // E <= 1024 = blockDim
   int c = 0;
@@ -109,6 +148,8 @@ __global__ __launch_bounds__(kScanThreads) void route_scan_kernel(
     offsets[E] = valid_total;
     active[0] = n_active;
   }
+  // (the word may be hist[0], whose 0 the scatter does not read)
+  if (choice.word) write_row_choice(choice, c, n_active, valid_total, s_blocks);
 }
 
 __global__ __launch_bounds__(kRouteThreads) void route_scatter_kernel(
@@ -136,7 +177,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_scatter_kernel(
   __syncthreads();
   // turn counts into starting rows: offsets[e] + earlier chunks + earlier waves
   for (int e = tid; e < E; e += kRouteThreads) {
-    int a = offsets[e] + hist[(size_t)blk * E + e];
+    int a = offsets[e] + (blk ? hist[(size_t)blk * E + e] : 0);
 #pragma unroll
     for (int w = 0; w < kWavesPerRouteBlock; ++w) {
       const int cw = next[w][e];
@@ -195,7 +236,8 @@ template <int STEPS>
 __global__ __launch_bounds__(kScanThreads) void route_fused_kernel(
     const int32_t* __restrict__ ids, int R, int E, int nbits, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ active, int32_t* __restrict__ perm,
-    int32_t* __restrict__ inv) {
+    int32_t* __restrict__ inv, RowChoice choice) {
+  __shared__ int s_blocks[2];
   __shared__ int next[kFusedWaves * kMaxExperts];  // [w][e], counts then starting rows
   __shared__ int s_wave[kScanThreads / kWave + 1];
   __shared__ int s_act[kMaxExperts];
@@ -251,6 +293,7 @@ __global__ __launch_bounds__(kScanThreads) void route_fused_kernel(
     offsets[E] = valid_total;
     active[0] = n_active;
   }
+  if (choice.word) write_row_choice(choice, c, n_active, valid_total, s_blocks);
   // stable ranks, 64 slots per step, steps in slot order (as route_scatter)
   const uint64_t lt = lanemask_lt();
 #pragma unroll
@@ -284,7 +327,7 @@ __global__ __launch_bounds__(kScanThreads) void route_fused_kernel(
 }  // namespace
 
 hipError_t launch_route_permute(const int32_t* ids, int R, int E,
-                                const eaas_routing& r, int32_t* hist,
+                                const eaas_routing& r, int32_t* hist, const RowChoice& choice,
                                 hipStream_t stream) {
   const int nblk = route_blocks(R);
   int nbits = 1;
@@ -292,19 +335,27 @@ hipError_t launch_route_permute(const int32_t* ids, int R, int E,
   if (R <= kFusedMaxSlots) {
     if (R <= 2 * kScanThreads)
       hipLaunchKernelGGL(route_fused_kernel<2>, dim3(1), dim3(kScanThreads), 0, stream, ids, R, E,
-                         nbits, r.counts, r.offsets, r.active, r.perm, r.inv);
+                         nbits, r.counts, r.offsets, r.active, r.perm, r.inv, choice);
     else
       hipLaunchKernelGGL(route_fused_kernel<kFusedMaxSlots / kScanThreads>, dim3(1),
                          dim3(kScanThreads), 0, stream, ids, R, E, nbits, r.counts, r.offsets,
-                         r.active, r.perm, r.inv);
+                         r.active, r.perm, r.inv, choice);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(route_hist_kernel, dim3(nblk), dim3(kRouteThreads), 0, stream,
                      ids, R, E, hist);
   hipLaunchKernelGGL(route_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream,
-                     hist, nblk, E, r.counts, r.offsets, r.active);
+                     hist, nblk, E, r.counts, r.offsets, r.active, choice);
   hipLaunchKernelGGL(route_scatter_kernel, dim3(nblk), dim3(kRouteThreads), 0, stream,
                      ids, R, E, nbits, hist, r.offsets, r.perm, r.inv);
+  return hipGetLastError();
+}
+
+hipError_t launch_row_choice(const int32_t* offsets, int R, int E, const RowChoice& choice,
+                             hipStream_t stream) {
+  if (choice.word == nullptr) return hipSuccess;
+  hipLaunchKernelGGL(row_choice_kernel, dim3(1), dim3(kScanThreads), 0, stream, offsets, R, E,
+                     choice);
   return hipGetLastError();
 }
 

@@ -103,7 +103,7 @@ def _bind(L: ctypes.CDLL) -> ctypes.CDLL:
     L.eaas_quantize_rows_fp8.restype = i32
     L.eaas_workspace_region.argtypes = [sp, i32, i32, ctypes.POINTER(sz), ctypes.POINTER(sz)]
     L.eaas_workspace_region.restype = i32
-    L.eaas_internal_gemm_plan.argtypes = [sp, i32, i32, i32]
+    L.eaas_internal_gemm_plan.argtypes = [sp, i32, i32, i32, vp]
     L.eaas_internal_gemm_plan.restype = i32
     L.eaas_status_string.argtypes = [i32]
     L.eaas_status_string.restype = ctypes.c_char_p
@@ -227,17 +227,20 @@ def eaas_workspace_bytes_for(T, H, I, E, k, w_dtype, entry) -> int:
 _GEMM_PATHS = ("tiled", "one_wave", "few", "wide8", "wide4", "tiled_a8", "stream_a8")
 
 
-def _gemm_plan(T, H, I, E, k, w_dtype, gate_up, capacity=False) -> tuple[str, bool]:
+def _gemm_plan(T, H, I, E, k, w_dtype, gate_up, capacity=False,
+               counts=None) -> tuple[str, bool, bool]:
     """(kernel path of the gate/up or down GEMM of a batch of these sizes,
-    whether that launch also routes the batch): the library's own dispatch,
-    asked on the host, for tests and measurements.  capacity: T is a dynamic
-    batch's capacity."""
+    whether that launch also routes the batch, whether the batch's rows decide
+    between that path and the tiled kernels): the library's own dispatch, asked
+    on the host, for tests and measurements.  capacity: T is a dynamic batch's
+    capacity.  counts: rows of each expert, for which the choice is made."""
     s = _shape(T, H, I, E, k)
+    c = None if counts is None else (ctypes.c_int32 * E)(*[int(n) for n in counts])
     r = int(lib().eaas_internal_gemm_plan(ctypes.byref(s), int(w_dtype), int(capacity),
-                                          int(gate_up)))
+                                          int(gate_up), c))
     if r < 0:
         raise EaasError(-2, "eaas_internal_gemm_plan")
-    return _GEMM_PATHS[r & 15], bool(r & 16)
+    return _GEMM_PATHS[r & 15], bool(r & 16), bool(r & 32)
 
 
 def alloc_workspace(T, H, I, E, k, w_dtype=EAAS_BF16, device="cuda") -> torch.Tensor:

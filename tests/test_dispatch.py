@@ -35,11 +35,11 @@ def test_a_hot_expert_is_not_walked_in_series(wdt, capacity):
         for k in (1, 2, 4, 8, 64):
             for T in (1, 16, 32, 33, 64, 65, 128, 512, 2048):
                 for gate_up in (True, False):
-                    p, routes = eaas._gemm_plan(T, 512, 256, E, k, wdt, gate_up, capacity)
+                    p, routes, _ = eaas._gemm_plan(T, 512, 256, E, k, wdt, gate_up, capacity)
                     assert p != "one_wave" or T <= 32, (T, E, k)
                     assert not routes or T <= 64, (T, E, k)
-    assert eaas._gemm_plan(32, 2048, 128, 256, 8, wdt, True, capacity) == ("one_wave", True)
-    assert eaas._gemm_plan(64, 2048, 512, 32, 8, wdt, True, capacity) == ("few", True)
+    assert eaas._gemm_plan(32, 2048, 128, 256, 8, wdt, True, capacity)[:2] == ("one_wave", True)
+    assert eaas._gemm_plan(64, 2048, 512, 32, 8, wdt, True, capacity)[:2] == ("few", True)
 
 
 @pytest.mark.parametrize("wdt", [BF16, FP8, eaas.EAAS_FP8_E4M3_TILED])
@@ -51,12 +51,80 @@ def test_self_routing_grids_fit_the_chip(wdt):
         for k in (1, 2, 6, 8):
             for I in (128, 640, 768, 2048, 14336):
                 for T in (1, 2, 3, 4, 8, 16, 17, 32, 33, 64):
-                    p, routes = eaas._gemm_plan(T, 1024, I, E, k, wdt, True)
+                    p, routes, _ = eaas._gemm_plan(T, 1024, I, E, k, wdt, True)
                     waves = min(E, T * k) * 2 * I // 32
                     assert not (routes and p == "few") or waves <= 2048, (T, E, k, I)
-    assert eaas._gemm_plan(16, 1024, 1024, 32, 8, wdt, True) == ("few", True)  # 2 048 waves
-    assert eaas._gemm_plan(16, *DSV3, wdt, True) == ("few", False)             # 4 096
-    assert eaas._gemm_plan(8, *DSV3, wdt, True) == ("one_wave", True)
+    assert eaas._gemm_plan(16, 1024, 1024, 32, 8, wdt, True)[:2] == ("few", True)  # 2 048 waves
+    assert eaas._gemm_plan(16, *DSV3, wdt, True)[:2] == ("few", False)             # 4 096
+    assert eaas._gemm_plan(8, *DSV3, wdt, True)[:2] == ("one_wave", True)
+
+
+MIXTRAL = (4096, 14336, 8, 2)
+
+
+def even(rows, E):
+    return [rows // E + (e < rows % E) for e in range(E)]
+
+
+@pytest.mark.parametrize("T,shape,wdt,gate_up,capacity,counts,expect", [
+    # a full dynamic batch takes the tiled kernels, a part-filled one streams
+    (1920, MIXTRAL, FP8, True, True, even(3840, 8), "tiled"),
+    (1920, MIXTRAL, FP8, True, True, even(890, 8), "wide8"),
+    (1920, MIXTRAL, FP8, False, True, even(3840, 8), "tiled"),
+    (1920, MIXTRAL, FP8, False, True, even(890, 8), "wide4"),
+    (2400, MIXTRAL, FP8, False, True, even(890, 8), "wide4"),
+    (512, QWEN3, BF16, True, True, even(4096, 128), "few"),
+    (768, QWEN3, BF16, True, True, even(6144, 128), "tiled"),
+    (768, QWEN3, BF16, True, True, even(3000, 128), "few"),
+    # hot experts: further blocks for one in four (bf16, 64 rows) or five (144 rows)
+    (512, QWEN3, BF16, True, True, [512] * 4 + even(2048, 124), "few"),
+    (512, QWEN3, BF16, True, True, [512] * 5 + even(1536, 123), "tiled"),
+    (384, QWEN3, BF16, True, False, [384] * 8 + [0] * 120, "tiled"),
+    (256, DSV3, FP8, True, False, even(2048, 32), "wide8"),
+    (256, DSV3, FP8, True, False, [145] * 6 + even(1178, 26), "wide8"),
+    (256, DSV3, FP8, True, False, [145] * 7 + even(1033, 25), "tiled"),
+    # few active experts: the blocks fill the chip no more than once
+    (256, DSV3, FP8, True, False, [256] * 8 + [0] * 24, "wide8"),
+    (300, DSV3, FP8, True, False, [300] * 8 + [0] * 24, "tiled"),
+    (768, QWEN3, FP8, True, True, [600] * 30 + [0] * 98, "tiled"),
+    (300, (384, 128, 5, 2), BF16, True, False, [300, 300, 0, 0, 0], "wide4"),
+    # no choice where an expert has one block, or further ones are few
+    (64, DSV3, FP8, True, False, [64] * 8 + [0] * 24, "few"),
+    (144, DSV3, FP8, True, False, [144] * 8 + [0] * 24, "wide8"),
+    (480, DSV3, FP8, False, False, even(3840, 32), "tiled")])
+def test_rows_choose_the_kernel(T, shape, wdt, gate_up, capacity, counts, expect):
+    assert eaas._gemm_plan(T, *shape, wdt, gate_up, capacity, counts)[0] == expect
+
+
+@pytest.mark.parametrize("wdt", [BF16, FP8, eaas.EAAS_FP8_E4M3_TILED])
+@pytest.mark.parametrize("shape", [QWEN3, DSV3, MIXTRAL, (1920, 640, 24, 6), (2048, 512, 256, 1)])
+def test_full_and_skewed_batches_are_not_streamed_block_after_block(shape, wdt):
+    """Whatever the batch, streaming launches that read an active expert's
+    weights more than twice fill the chip no more than once (N a multiple of
+    256), and a dynamic batch of the same rows takes the kernels of a plain one
+    or streams where that is left to it."""
+    H, I, E, k = shape
+    if wdt == eaas.EAAS_FP8_E4M3_TILED and H % 256:
+        pytest.skip("the tiled layout needs H a multiple of 256")
+    for T in (65, 145, 200, 256, 257, 384, 512, 1024, 1920, 4096):
+        hot = [T] * min(k, E) + [0] * (E - min(k, E))
+        half = [T // 2] * min(2 * k, E) + [0] * (E - min(2 * k, E))
+        for counts in (even(T * k, E), hot, half):
+            for gate_up, N in ((True, 2 * I), (False, H)):
+                if N % 256:
+                    continue
+                for capacity in (False, True):
+                    p = eaas._gemm_plan(T, *shape, wdt, gate_up, capacity, counts)[0]
+                    height = {"few": 64, "one_wave": 32, "wide8": 144, "wide4": 144}.get(p)
+                    if height is None or (p == "few" and T <= 256 and T * k <= 16 * E):
+                        continue
+                    active = sum(c > 0 for c in counts)
+                    blocks = sum(-(-c // height) for c in counts)
+                    cols, slots = {"few": (128, 512), "one_wave": (32, 2048), "wide8": (256, 256),
+                                   "wide4": (128, 256)}[p]
+                    spare = 4 / 3 if p == "few" and wdt != BF16 else 5 / 4
+                    assert blocks <= spare * active or blocks * (N // cols) <= slots, (
+                        T, p, gate_up, capacity, counts[:10])
 
 
 def test_a_long_list_of_experts_needs_a_long_k():

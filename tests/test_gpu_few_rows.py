@@ -180,3 +180,54 @@ def test_fp8_activations_of_few_tokens(gpu, T, k, E, H, I):
     got = run(few, k, eaas.EAAS_FP8_E4M3_A8)
     assert np.isfinite(got).all()
     assert np.array_equal(got.view(np.uint32), whole[:T].view(np.uint32))
+
+
+# path: E, k, H, I, capacity, tokens of a batch that streams
+CHOICES = {
+    "few": (160, 2, 512, 256, 3500, 1200),
+    "wide8": (72, 2, 512, 512, 5000, 2000),
+    "wide4": (8, 2, 512, 512, 4000, 800),
+    "few, N % 256": (160, 2, 384, 256, 3500, 1200),  # (down: few alone)
+}
+
+
+@pytest.mark.parametrize("case", list(CHOICES))
+@pytest.mark.parametrize("wdtype", ["bf16", "fp8"])
+def test_the_rows_choose_between_streaming_and_tiled(gpu, case, wdtype):
+    """A dynamic batch whose capacity leaves the kernel open: part filled it
+    streams, full it takes the tiled kernels, and so it does with half the
+    experts empty and the rest twice as full.  Each request's rows are bit for
+    bit those of the plain step on the same tokens, and near the oracle's."""
+    E, k, H, I, cap, some = CHOICES[case]
+    path = case.split(",")[0]
+    if path == "wide8" and wdtype == "bf16":
+        pytest.skip("bf16 gate/up of many tiles takes the tiled kernel")
+    print(f"rows choose: {case} {wdtype}", flush=True)
+    wdt = eaas.EAAS_BF16 if wdtype == "bf16" else eaas.EAAS_FP8_E4M3
+    d = synth.make_inputs(cap, H, I, E, k, 80, wdtype=wdtype)
+    for tokens, crowded, expect in ((some, False, path), (cap, False, "tiled"),
+                                    (cap, True, "tiled")):
+        sub = O.sub_batch(d, np.arange(tokens))
+        if crowded:
+            sub["topk_ids"] = (sub["topk_ids"] // 2).astype(np.int32)
+        counts = np.bincount(sub["topk_ids"].ravel(), minlength=E)
+        assert eaas._gemm_plan(cap, H, I, E, k, wdt, True, True, counts)[0] == expect
+        dev = to_device(sub)
+        whole = run(dev, k, wdt)
+        n0 = tokens // 3
+        out = torch.full((tokens, H), float("nan"), dtype=torch.float32, device="cuda")
+        bufs = [tuple(dev[key][a:b].clone() for key in ("x", "topk_ids", "topk_weights")) + (out[a:b],)
+                for a, b in ((0, n0), (n0, tokens))]
+        table = eaas.segment_table(bufs)
+        sizes = torch.tensor([n0, tokens - n0], dtype=torch.int32, device="cuda")
+        ws = eaas.alloc_segments_workspace(cap, H, I, E, k, wdt)
+        ws.fill_(0xFF)
+        eaas.eaas_expert_forward_segments(table, sizes, 2, cap, k, dev["w_gate_up"],
+                                          dev["w_down"], ws, eaas.EAAS_FP32,
+                                          dev["w_gate_up_scale"], dev["w_down_scale"])
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert np.array_equal(got.view(np.uint32), whole.view(np.uint32)), (tokens, crowded)
+    ref = O.expert_forward(sub)["out"]
+    rms = float(np.sqrt((ref ** 2).mean()))
+    assert float(np.abs(got - ref).max()) <= TOL * rms
