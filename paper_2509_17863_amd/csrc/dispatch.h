@@ -61,19 +61,20 @@ constexpr int kWideRows = 144;
 // list needs a long K (whole step, tiled / row blocks: H 1024, I 256, E 1024,
 // k 1, 2048 tokens: fp8 210 / 294 us, bf16 306 / 340; H 4096, I 1024, E 512,
 // k 8, 96 tokens, fp8: 954 / 809).
-// One 144-row block per expert: the fp8 gate/up GEMM, whose tiled kernel needs a second tile past
-// 96 rows: dsv3 shape 64 slots 209 -> 182 us, 64 with Zipf 1.2 302 -> 264, 96:
-// 327 -> 239; at 128 it is 336 -> 355.  (The down GEMM's smaller tiled
-// workgroups are as fast: 64: 132 -> 129, 96: 163 -> 159.)
+// One 144-row block per expert: the fp8 gate/up GEMM, whose tiled kernel needs a
+// second tile past 96 rows: dsv3 shape 64 slots 209 -> 182 us, 64 with Zipf 1.2
+// 302 -> 264, 96: 327 -> 239; at 128 it is 336 -> 355.  (The down GEMM's smaller
+// tiled workgroups are as fast: 64: 132 -> 129, 96: 163 -> 159.)
 // The same where 128-row tiles at most fill the chip once, so that the tiled
 // kernels' 256-row ones leave half of it idle: down GEMM, mixtral shape, bf16
 // 64 slots 281 -> 185 us, 128: 288 -> 222, fp8 111: 227 -> 187; a bf16 gate/up
 // of 8 experts x 1 024 rows, 64 slots: 33 -> 27.
-// N no multiple of 256: the streaming kernel alone up to 350 slots per expert
-// or two rounds of its blocks (whole step, H 1920, I 640, E 24, k 6: 200 slots
-// 103 against 101 us with the tiled kernel for N / 256 tiles and the streaming
-// one for the rest, 300: 137 against 131, 500: 201 against 214; H 384, I 128,
-// E 5, k 2, 280 slots: 43 against 32).
+// N no multiple of 256: the streaming kernel alone up to 350 slots per expert or
+// two rounds of its blocks, past that the tiled kernel for N / 256 tiles and the
+// streaming one for the rest (whole step, H 1920, I 640, E 24, k 6, alone / both,
+// bf16: 250 slots 109 / 112 us, 300: 120 / 125, 350: 138 / 135, 500: 214 / 201;
+// fp8: 250: 127 / 128, 300: 142 / 141, 350: 161 / 153; H 384, I 128, E 5, k 2,
+// 280 slots: 32 / 43).
 inline GemmPath stream_path(const FfnArgs& a, bool gateup) {
   const long long R = (long long)a.T * a.k, N = gateup ? 2LL * a.I : a.H;
   const bool few = R <= (a.capacity ? 48 : a.fp8 ? 32 : 24) * (long long)a.E;
