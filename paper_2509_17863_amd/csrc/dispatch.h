@@ -121,14 +121,17 @@ inline RowRule row_rule(const FfnArgs& a, bool gateup, GemmPath path) {
 
 // fp8 activations: the streaming kernel takes the gate/up GEMM of up to 4
 // tokens and the down GEMM of up to 16, where an expert has one 16-row block.
-// Gate/up has the same workgroups per 128 columns of h either way, so it gains
-// little and loses where an expert's rows differ in every wave's loads (dsv3
-// shape, ids of 8 servers, 8 tokens: 94 us per step tiled, 96 with both
-// streamed; Zipf 1.2, 16 tokens: 207 and 218).  The down GEMM has 256-row
-// tiles to spread over the chip.  Steps, tiled -> streaming, same run: mixtral
-// shape 1 token 162 -> 86 us, 4 tokens 248 -> 186, 16 tokens 328 -> 296; qwen3
-// shape 42 -> 32, 48 -> 40, 118 -> 105; dsv3 shape 92 -> 88, 203 -> 191,
-// 247 -> 229, with Zipf 1.2 routing 207 -> 199.
+// Gate/up has the same workgroups per 128 columns of h either way, so what it
+// gains is the routing launch, and it loses where every wave's loads of long
+// rows are many (step, tiled / streamed gate/up, both with a streamed down: qwen3
+// shape, 4 tokens, 42.7 / 39.1 us; mixtral shape, H 4096, not routed inside: 3
+// tokens 199 / 190, 4 tokens 207 / 205; dsv3 shape, H 7168, not routed inside: 3
+// tokens with ids of 8 servers 77 / 81, 4 tokens Zipf 1.2 176 / 186, 4 equal
+// tokens 90 / 98, against 92 with nothing streamed).  So: where it routes, or up
+// to H 4096.  From 5 tokens on (down streamed alone, nothing streamed / that):
+// dsv3 shape, 5 tokens 209 / 196, 8 tokens 217 / 205, with ids of 8 servers 98 /
+// 93, Zipf 1.2 186 / 179, 16 tokens 247 / 230, Zipf 1.2 212 / 206, 16 equal tokens
+// 94 / 97; qwen3 shape, 8 tokens 81 / 73; mixtral shape, 8 tokens 332 / 298.
 inline GemmPlan gemm_plan(const FfnArgs& a, bool gateup) {
   const long long R = (long long)a.T * a.k;
   if (!a.act8) {
@@ -147,16 +150,15 @@ inline GemmPlan gemm_plan(const FfnArgs& a, bool gateup) {
                       (path == kPathOneWave || (path == kPathFew && waves <= 2048)),
             row_rule(a, gateup, path)};
   }
-  const bool stream = a.T <= (gateup ? 4 : 16);
   // Routing inside the launch only where one workgroup per CU covers every
   // slot's columns: the groups without rows are not compacted away, and with
   // more workgroups than CUs the ones that have work pile up on some of them
   // (dsv3 shape, 16 tokens with ids of 8 servers: 167 us, compacted by the
   // routing launch 119, tiled 125; qwen3 shape, 16 tokens, Zipf 1.2: 59, tiled
   // 51).
-  return {stream ? kPathStreamA8 : kPathTiledA8,
-          gateup && stream && R <= kSelfSlots && R <= a.E && R * (2 * a.I / 256) <= 256,
-          RowRule{0, 0, 0, 0}};
+  const bool routes = gateup && a.T <= 4 && R <= kSelfSlots && R <= a.E && R * (2 * a.I / 256) <= 256;
+  const bool stream = gateup ? a.T <= 4 && (routes || a.H <= 4096) : a.T <= 16;
+  return {stream ? kPathStreamA8 : kPathTiledA8, routes, RowRule{0, 0, 0, 0}};
 }
 
 }  // namespace eaas

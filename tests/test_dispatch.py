@@ -19,7 +19,9 @@ def path(T, shape, wdt, gate_up=True, capacity=False):
     (1, DSV3, FP8, True, "one_wave"), (9, DSV3, FP8, True, "few"),
     (9, DSV3, BF16, False, "few"), (256, DSV3, FP8, True, "wide8"),
     (256, DSV3, FP8, False, "tiled"), (8192, QWEN3, BF16, True, "tiled"),
-    (4, DSV3, A8, True, "stream_a8"), (5, DSV3, A8, True, "tiled_a8"),
+    (2, DSV3, A8, True, "stream_a8"), (5, QWEN3, A8, True, "tiled_a8"),
+    # 3 tokens x 8 slots x 16 column blocks: not routed inside, and H is long
+    (3, DSV3, A8, True, "tiled_a8"), (4, (4096, 14336, 8, 2), A8, True, "stream_a8"),
     (16, DSV3, A8, False, "stream_a8"), (17, DSV3, A8, False, "tiled_a8")])
 def test_paths(T, shape, wdt, gate_up, expect):
     assert path(T, shape, wdt, gate_up) == expect
