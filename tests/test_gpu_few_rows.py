@@ -5,7 +5,8 @@ tile, an odd number of 128-channel blocks and several ring lengths.
 
 Against the oracle, and bit for bit against the same tokens inside a batch
 large enough for the tiled kernels (a token's result does not depend on the
-batch around it).
+batch around it); the tests ask the library's dispatch that they run what they
+name.
 """
 import numpy as np
 import pytest
@@ -18,12 +19,12 @@ from paper_2509_17863_amd.device_io import to_device
 pytestmark = pytest.mark.gpu
 TOL = 2e-2
 
-# rows per expert; the rest of the E experts stay empty.  "alone" has at most
-# two rows per expert on average (one wave per workgroup), "shared" more, and
-# "wide" enough for 144-row blocks (with 64 experts and I 384, more 128-row
-# weight tiles than CUs).
+# rows per expert; the rest of the E experts stay empty.  "sparse" and "shared"
+# take 64-row blocks, the first with few rows per expert and more than 64 active
+# ones, and "wide" has enough for 144-row blocks (with 64 experts and I 384, more
+# 128-row weight tiles than CUs).
 EDGES = {
-    "alone": (128, [33, 17, 16, 15, 2] + [1] * 68),
+    "sparse": (128, [33, 17, 16, 15, 2] + [1] * 68),
     "shared": (100, [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 97, 130, 0, 2] + [3] * 60),
     "one expert": (1, [20]),
     "wide": (64, [143, 144, 145, 288, 289, 96, 97, 112, 113, 128, 129, 1, 16, 17] + [40] * 50),
@@ -56,8 +57,9 @@ def test_row_counts_and_k_lengths(gpu, rows, wdtype, H, I):
     print(f"few rows: {rows} {wdtype} H={H} I={I} E={E} R={sum(counts)}", flush=True)
     rng = np.random.default_rng(len(counts) + H + I)
     small = rng.permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)
-    # past 120 slots per expert no streaming kernel runs (but for N's last 128 rows)
-    fill = (130 if rows.startswith("wide") else 49) * E + 200
+    # past 120 slots per expert no streaming kernel runs, but for the down GEMM of
+    # an H that is no multiple of 256 (test_the_last_128_rows_of_n has its tiled side)
+    fill = 130 * E + 200
     big = np.concatenate([small, rng.integers(0, E, fill).astype(np.int32)])
     d = synth.make_inputs(len(big), H, I, E, 1, 77, wdtype="bf16" if wdtype == "bf16" else "fp8")
     d["topk_ids"] = big[:, None].copy()
@@ -65,6 +67,14 @@ def test_row_counts_and_k_lengths(gpu, rows, wdtype, H, I):
     sub = O.sub_batch(d, np.arange(len(small)))
     wdt = {"bf16": eaas.EAAS_BF16, "fp8": eaas.EAAS_FP8_E4M3,
            "tiled": eaas.EAAS_FP8_E4M3_TILED}[wdtype]
+    for gate_up in (True, False):
+        p = eaas._gemm_plan(len(big), H, I, E, 1, wdt, gate_up)[0]
+        assert p == ("wide4" if H % 256 and not gate_up else "tiled")
+        p = eaas._gemm_plan(len(small), H, I, E, 1, wdt, gate_up)[0]
+        if not rows.startswith("wide"):
+            assert p == "few"
+        elif gate_up and wdtype != "bf16":
+            assert p in ("wide8", "wide4")
 
     def device(inp):
         dev = to_device(inp)
@@ -180,6 +190,38 @@ def test_fp8_activations_of_few_tokens(gpu, T, k, E, H, I):
     got = run(few, k, eaas.EAAS_FP8_E4M3_A8)
     assert np.isfinite(got).all()
     assert np.array_equal(got.view(np.uint32), whole[:T].view(np.uint32))
+
+
+@pytest.mark.parametrize("H,I,E,counts", [
+    (1920, 128, 4, [1, 255, 2000, 3744]),    # 7 whole tiles and 128 rows
+    (384, 256, 3, [20000, 129, 4900]),       # 1 and 128
+    (640, 128, 6, [0, 15000, 257, 0, 96, 97])])
+@pytest.mark.parametrize("wdtype", ["bf16", "fp8"])
+def test_the_last_128_rows_of_n(gpu, H, I, E, counts, wdtype):
+    """N no multiple of 256 in a large batch: the tiled kernel takes N / 256
+    tiles and a streaming launch the last 128 rows of the down matrix.  Bit for
+    bit against small batches of the same tokens, which stream alone, and
+    against the oracle."""
+    print(f"last rows of N: {wdtype} H={H} I={I} E={E} R={sum(counts)}", flush=True)
+    wdt = eaas.EAAS_BF16 if wdtype == "bf16" else eaas.EAAS_FP8_E4M3
+    R = sum(counts)
+    assert eaas._gemm_plan(R, H, I, E, 1, wdt, False)[0] == "tiled"
+    rng = np.random.default_rng(H)
+    d = synth.make_inputs(R, H, I, E, 1, 82, wdtype=wdtype)
+    ids = rng.permutation(np.repeat(np.arange(E), counts)).astype(np.int32)
+    d["topk_ids"] = ids[:, None].copy()
+    d["topk_weights"] = rng.uniform(0.2, 1.0, (R, 1)).astype(np.float32)
+    whole = run(to_device(d), 1, wdt)
+    # tokens of every expert: the first, the last and some between
+    pick = np.unique(np.concatenate([np.flatnonzero(ids == e)[[0, -1]] for e in range(E)
+                                     if counts[e]] + [rng.choice(R, 300, replace=False)]))
+    sub = O.sub_batch(d, pick)
+    assert eaas._gemm_plan(len(pick), H, I, E, 1, wdt, False)[0] == "wide4"
+    got = run(to_device(sub), 1, wdt)
+    assert np.array_equal(got.view(np.uint32), whole[pick].view(np.uint32))
+    ref = O.expert_forward(sub)["out"]
+    rms = float(np.sqrt((ref ** 2).mean()))
+    assert float(np.abs(whole[pick] - ref).max()) <= TOL * rms
 
 
 # path: E, k, H, I, capacity, tokens of a batch that streams

@@ -458,15 +458,20 @@ TILE_EDGE_COUNTS = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 255, 2
 
 
 @pytest.mark.parametrize("wdtype", ["bf16", "fp8"])
-@pytest.mark.parametrize("H,extra", [(128, 0), (384, 0), (256, 3000)])
+@pytest.mark.parametrize("H,extra", [(128, 0), (384, 0), (256, 700), (768, 700), (256, 3000)])
 def test_forward_tile_row_boundaries(gpu, wdtype, H, extra):
     """Experts holding one row less than, exactly, and one row more than a
     32-row block, a 96-row fp8 tile, a half (128-row) and a whole (256-row)
-    bf16 tile.  Without `extra` the batch is decode-sized (R <= 256 E: the
-    small-tile weight ring and the nontemporal weight reads); an extra expert
-    with `extra` rows makes it prefill-sized.  K = H gives 2, 6 and 4 K tiles."""
+    bf16 tile.  Without `extra` the batch streams; an extra expert with 700 rows
+    makes it one of the tiled kernels, decode-sized (R <= 256 E: the small-tile
+    weight ring and the nontemporal weight reads), one with 3 000 rows
+    prefill-sized.  K = H gives 2, 6, 4 and 12 K tiles."""
     counts = TILE_EDGE_COUNTS + ([extra] if extra else [])
     E, T, I = len(counts), int(sum(counts)), 128
+    wdt = eaas.EAAS_BF16 if wdtype == "bf16" else eaas.EAAS_FP8_E4M3
+    for gate_up in (True, False):
+        assert eaas._gemm_plan(T, H, I, E, 1, wdt, gate_up)[0] == ("tiled" if extra else "wide4")
+    assert extra == 3000 or T <= 256 * E
     rng = np.random.default_rng(40 + H + extra)
     d = synth.make_inputs(T, H, I, E, 1, 41, zipf=None, wdtype=wdtype)
     ids = np.repeat(np.arange(E, dtype=np.int32), counts)
@@ -644,8 +649,8 @@ def test_forward_k_above_E(gpu):
 
 
 @pytest.mark.parametrize("shape", [(300, 256, 256, 1024, 8, 83, None, "bf16"),
-                                   (700, 512, 384, 40, 4, 84, 1.5, "bf16"),
-                                   (200, 512, 256, 12, 4, 85, 1.2, "fp8")])
+                                   (1300, 512, 384, 40, 4, 84, 1.5, "bf16"),
+                                   (400, 512, 256, 12, 4, 85, 1.2, "fp8")])
 def test_scheduler_builds_agree_bitwise(gpu, shape):
     """The two other builds of the GEMM tile scheduler (all E experts
     scanned; every workgroup walking the E experts) find the same tiles:
@@ -653,6 +658,9 @@ def test_scheduler_builds_agree_bitwise(gpu, shape):
     from paper_2509_17863_amd import _build
 
     T, H, I, E, k, seed, zipf, wdtype = shape
+    wdt = eaas.EAAS_BF16 if wdtype == "bf16" else eaas.EAAS_FP8_E4M3
+    for gate_up in (True, False):  # (only the tiled kernels have the scheduler)
+        assert eaas._gemm_plan(T, H, I, E, k, wdt, gate_up)[0] == "tiled"
     d = synth.make_inputs(T, H, I, E, k, seed, zipf=zipf, wdtype=wdtype)
     dev = to_device(d)
     say("scheduler builds", shape)
