@@ -7,8 +7,9 @@
 // weight rows per workgroup and a whole CU per workgroup: with few active
 // experts most CUs hold nothing, and with many the start and the end of every
 // tile leave its CU idle.  Here a wave owns 32 weight rows (gate/up: 16 gate
-// rows and the matching 16 up rows) and a ring of D K tiles in registers, so
-// 16 KiB or more are in flight per wave and eight waves share a CU:
+// rows and the matching 16 up rows) and a ring of D K tiles of 4 KiB in
+// registers, so 8 to 32 KiB are in flight per wave, and four (wide4) or eight
+// waves share a CU:
 //
 //   grouped_gemm_stream_kernel  one wave per workgroup, token rows loaded like
 //                               the weights; no LDS, no barrier (a row or two
@@ -427,8 +428,9 @@ __device__ __forceinline__ void stream_tile(const GemmParams& p, int e, const Bl
   else store_rows<KIND, MB>(p, b.rows, c0, orow, acc);
 }
 
-// All rows of an expert, 32 at a time, times one wave's weights.  (A ring of 8 K tiles with 16 rows,
-// 5 with 32: 4 and 3 were within 3%; past 256 registers fewer waves would fit.)
+// All rows of an expert, 32 at a time, times one wave's weights.  (bf16: a ring
+// of 8 K tiles with 16 rows, 5 with 32: 4 and 3 were within 3%; past 256
+// registers fewer waves would fit.)
 template <int KIND, int W>
 __device__ __forceinline__ void stream_rows(const GemmParams& p, int e, const BlockRows& all,
                                             int wt) {
@@ -799,9 +801,8 @@ template <int W>
 struct Few {
   static constexpr int NW = 4, MBX = 4, D = 4, OCC = 2;
 };
-template <int W>
-struct Wide8 {
-  static constexpr int NW = 8, MBX = 9, D = W == kBf16Rows ? 4 : 2, OCC = 2;
+struct Wide8 {  // fp8 gate/up
+  static constexpr int NW = 8, MBX = 9, D = 2, OCC = 2;
 };
 template <int W>
 struct Wide4 {
@@ -926,7 +927,9 @@ void grouped_gemm_stream_a8_kernel(GemmParams p) {
 
 template <int KIND, int W>
 hipError_t enqueue(const GemmParams& p, int R, int E, GemmPath path, hipStream_t stream) {
-  if (path == kPathWide8) return launch_shared<KIND, W, Wide8<W>>(p, R, E, stream);
+  if constexpr (KIND == kGateUp && W != kBf16Rows) {
+    if (path == kPathWide8) return launch_shared<KIND, W, Wide8>(p, R, E, stream);
+  }
   if (path == kPathWide4) return launch_shared<KIND, W, Wide4<W>>(p, R, E, stream);
   const bool self = KIND == kGateUp && p.ids != nullptr;
   if (path == kPathFew && !self) return launch_shared<KIND, W, Few<W>>(p, R, E, stream);
