@@ -246,7 +246,9 @@ int eaas_expert_forward(const eaas_shape *s, const void *x,
  * hipEvent_t handles (passed as void*, NULL entries skipped) recorded on
  * `stream` before routing, before the gate/up GEMM, before the down GEMM,
  * before the combine and after it.  events itself may be NULL.  Same kernels,
- * same results as eaas_expert_forward. */
+ * same results as eaas_expert_forward.  (Small batches are routed inside the
+ * gate/up launch: their routing interval is empty, and the gate/up interval
+ * holds both.) */
 int eaas_expert_forward_profiled(const eaas_shape *s, const void *x,
                                  const int32_t *topk_ids,
                                  const float *topk_weights,

@@ -344,7 +344,7 @@ int eaas_expert_forward_profiled(const eaas_shape* s, const void* x, const int32
   a.y = stage;
   a.epilogue = kDownBySlot;
   // (fp8 activations: x is quantized in the routing interval, so the gate/up
-  // interval times the GEMM alone)
+  // interval times the GEMM alone, or with the routing where the launch does it)
   hipError_t e = before_gate_up(a, topk_ids, rt, base, L, hs);
   if (e != hipSuccess || mark(1) != hipSuccess) return EAAS_ERR_HIP;
   e = launch_gate_up(a, hs);
