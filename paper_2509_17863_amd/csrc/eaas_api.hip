@@ -573,8 +573,9 @@ int eaas_expert_forward_noalloc(const eaas_shape* s, const void* x, const int32_
 // Not part of the ABI: the kernels a batch takes, for tests and measurements.
 // Returns the GemmPath of the GEMM plus 16 if its launch also routes the batch
 // (entry points that take ids) and 32 if the rows decide between that path and
-// the tiled kernels; or -1 for what the library rejects.  counts (optional,
-// host): rows of each of the E experts, for which the choice is made.
+// the tiled kernels, then plus 256 times the row blocks that the streaming launch
+// has room for; or -1 for what the library rejects.  counts (optional, host):
+// rows of each of the E experts, for which the choice is made.
 int eaas_internal_gemm_plan(const eaas_shape* s, int w_dtype, int capacity, int gate_up,
                             const int32_t* counts) {
   if (check_shape(s) != EAAS_OK || !known_wdtype(w_dtype) ||
@@ -597,7 +598,7 @@ int eaas_internal_gemm_plan(const eaas_shape* s, int w_dtype, int capacity, int 
     }
     if (!rows_stream(plan.rule, active, blocks, rows)) path = kPathTiled;
   }
-  return path + (plan.routes ? 16 : 0) + (rule ? 32 : 0);
+  return path + (plan.routes ? 16 : 0) + (rule ? 32 + 256 * most_blocks(plan.rule, a.E) : 0);
 }
 
 const char* eaas_status_string(int status) {

@@ -1504,6 +1504,7 @@ hipError_t launch_kind(GemmParams p, int R, int E, const GemmPlan& plan, const i
     if (choice == nullptr) return hipErrorInvalidValue;
     p.choice = choice;
     p.choice_bit = KIND == kGateUp ? 1 : 2;
+    p.most_blocks = most_blocks(plan.rule, E);
   }
   const hipError_t e = launch_gemm_stream<KIND, FP8>(p, R, E, plan.path, stream);
   if (e != hipSuccess || p.choice == nullptr) return e;

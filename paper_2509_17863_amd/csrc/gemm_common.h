@@ -58,6 +58,7 @@ struct GemmParams {
   const int32_t* choice;
   int choice_bit;
   bool tiled_launch;
+  int most_blocks;        // row blocks of the streaming launch, if it runs
 };
 
 // Whether the batch is the other launch's.

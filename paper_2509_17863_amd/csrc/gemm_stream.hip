@@ -866,8 +866,9 @@ template <int KIND, int W, class G>
 hipError_t launch_shared(const GemmParams& p, int R, int E, hipStream_t stream) {
   constexpr int ROWS = 16 * G::MBX;
   if (p.N % (32 * G::NW)) return hipErrorInvalidValue;
-  const long long grid =
-      ((long long)(R + ROWS - 1) / ROWS + std::min(E, R)) * (p.N / (32 * G::NW) - p.tn0);
+  long long blocks = (long long)(R + ROWS - 1) / ROWS + std::min(E, R);
+  if (p.choice && !p.tiled_launch) blocks = std::min<long long>(blocks, p.most_blocks);
+  const long long grid = blocks * (p.N / (32 * G::NW) - p.tn0);
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL((grouped_gemm_shared_kernel<KIND, W, G>), dim3((unsigned)grid),

@@ -31,6 +31,11 @@ __host__ __device__ inline bool rows_stream(const RowRule& r, int active, int bl
   return blocks <= r.one_round ||
          ((blocks - active) * r.spare <= active && rows <= r.mean * active);
 }
+// Most row blocks of a batch of E experts that streams.
+inline int most_blocks(const RowRule& r, int E) {
+  const int spread = r.spare > 0 ? E + E / r.spare : 0;
+  return r.one_round > spread ? r.one_round : spread;
+}
 // The rules of a batch's two GEMMs and where the choice is written: bit 0 if the
 // gate/up GEMM streams, bit 1 if the down GEMM does.
 struct RowChoice {

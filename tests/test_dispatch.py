@@ -1,7 +1,9 @@
 """Which kernels a batch takes (csrc/dispatch.h), asked on the host."""
+import ctypes
 import importlib.util
 import os
 
+import numpy as np
 import pytest
 
 from paper_2509_17863_amd import eaas, synth
@@ -127,6 +129,33 @@ def test_full_and_skewed_batches_are_not_streamed_block_after_block(shape, wdt):
                     spare = 4 / 3 if p == "few" and wdt != BF16 else 5 / 4
                     assert blocks <= spare * active or blocks * (N // cols) <= slots, (
                         T, p, gate_up, capacity, counts[:10])
+
+
+@pytest.mark.parametrize("wdt", [BF16, FP8])
+@pytest.mark.parametrize("shape", [QWEN3, DSV3, MIXTRAL, (512, 512, 72, 2), (512, 256, 160, 2)])
+def test_a_batch_that_streams_fits_the_streaming_launch(shape, wdt):
+    """The streaming launch of a batch whose rows decide has room for no more
+    row blocks than a batch that streams can have."""
+    H, I, E, k = shape
+    rng = np.random.default_rng(E)
+    chosen = 0
+    for T in (257, 300, 512, 1000, 3000):
+        for gate_up in (True, False):
+            s = eaas._shape(T, H, I, E, k)
+            r = eaas.lib().eaas_internal_gemm_plan(ctypes.byref(s), wdt, 1, int(gate_up), None)
+            if not r & 32:
+                continue
+            room, height = r >> 8, {2: 64, 3: 144, 4: 144}[r & 15]
+            for trial in range(300):
+                p = rng.dirichlet(np.full(E, 10.0 ** rng.uniform(-2, 2)))
+                counts = rng.multinomial(rng.integers(1, T * k + 1), p)
+                if trial % 3 == 0:  # blocks that are barely begun
+                    counts = np.minimum(counts // height * height + 1, T * k)
+                if eaas._gemm_plan(T, *shape, wdt, gate_up, True, counts)[0] == "tiled":
+                    continue
+                chosen += 1
+                assert -(-counts // height).sum() <= room
+    assert chosen
 
 
 def test_a_long_list_of_experts_needs_a_long_k():

@@ -273,3 +273,42 @@ def test_the_rows_choose_between_streaming_and_tiled(gpu, case, wdtype):
     ref = O.expert_forward(sub)["out"]
     rms = float(np.sqrt((ref ** 2).mean()))
     assert float(np.abs(got - ref).max()) <= TOL * rms
+
+
+@pytest.mark.parametrize("case", ["few", "wide4"])
+def test_a_captured_step_chooses_on_every_replay(gpu, case):
+    """One captured dynamic-batch step serves part-filled and full batches: the
+    choice between streaming and tiled kernels is made on the device, again on
+    every replay.  Each replay against an eager step with the same counts."""
+    E, k, H, I, cap, some = CHOICES[case]
+    print(f"captured choice: {case}", flush=True)
+    d = synth.make_inputs(cap, H, I, E, k, 83, wdtype="bf16")
+    dev = to_device(d)
+    out = torch.zeros((cap, H), dtype=torch.float32, device="cuda")
+    table = eaas.segment_table([(dev["x"], dev["topk_ids"], dev["topk_weights"], out)])
+    sizes = torch.tensor([some], dtype=torch.int32, device="cuda")
+    ws = eaas.alloc_segments_workspace(cap, H, I, E, k, eaas.EAAS_BF16)
+
+    def step():
+        eaas.eaas_expert_forward_segments(table, sizes, 1, cap, k, dev["w_gate_up"],
+                                          dev["w_down"], ws, eaas.EAAS_FP32)
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for tokens in (some, cap, some, some // 2, cap):
+        counts = np.bincount(d["topk_ids"][:tokens].ravel(), minlength=E)
+        assert eaas._gemm_plan(cap, H, I, E, k, eaas.EAAS_BF16, True, True, counts)[0] == (
+            "tiled" if tokens == cap else case)
+        sizes.fill_(tokens)
+        out.zero_()
+        step()
+        eager = out.clone()
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager), tokens
+        assert out[:tokens].abs().sum(dim=1).min().item() > 0
+        assert not out[tokens:].any().item()
