@@ -139,7 +139,7 @@ def test_a_batch_that_streams_fits_the_streaming_launch(shape, wdt):
     H, I, E, k = shape
     rng = np.random.default_rng(E)
     chosen = 0
-    for T in (257, 300, 512, 1000, 3000):
+    for T in (100, 150, 257, 300, 512, 1000, 3000):
         for gate_up in (True, False):
             s = eaas._shape(T, H, I, E, k)
             r = eaas.lib().eaas_internal_gemm_plan(ctypes.byref(s), wdt, 1, int(gate_up), None)
