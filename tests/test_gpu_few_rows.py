@@ -312,3 +312,41 @@ def test_a_captured_step_chooses_on_every_replay(gpu, case):
         assert torch.equal(out, eager), tokens
         assert out[:tokens].abs().sum(dim=1).min().item() > 0
         assert not out[tokens:].any().item()
+
+
+@pytest.mark.parametrize("wdtype", ["bf16", "fp8"])
+def test_the_rows_choose_in_the_separate_entry_points(gpu, wdtype):
+    """eaas_expert_ffn_grouped gets its routing from the caller and makes the
+    choice by itself: even routing streams, a quarter of the experts with all the
+    rows is tiled (bf16).  Bit for bit the whole step, and near the oracle."""
+    T, H, I, E, k = 1500, 512, 256, 160, 2
+    print(f"separate entry points choose: {wdtype}", flush=True)
+    wdt = eaas.EAAS_BF16 if wdtype == "bf16" else eaas.EAAS_FP8_E4M3
+    d = synth.make_inputs(T, H, I, E, k, 84, wdtype=wdtype)
+    paths = []
+    for crowd in (1, 4):
+        d["topk_ids"] = (d["topk_ids"] // crowd).astype(np.int32)
+        counts = np.bincount(d["topk_ids"].ravel(), minlength=E)
+        path, _, by_rows = eaas._gemm_plan(T, H, I, E, k, wdt, True, False, counts)
+        assert by_rows
+        paths.append(path)
+        dev = to_device(d)
+        whole = run(dev, k, wdt)
+        r = eaas.alloc_routing(T, k, E)
+        n = eaas.eaas_workspace_bytes_for(T, H, I, E, k, wdt, eaas.EAAS_ENTRY_FFN_GROUPED)
+        ws = torch.full((n + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        wsr = eaas.alloc_workspace(T, H, I, E, k, wdt)
+        y = torch.zeros((T * k, H), dtype=torch.float32, device="cuda")
+        out = torch.empty((T, H), dtype=torch.float32, device="cuda")
+        eaas.eaas_route_permute(dev["topk_ids"], E, r, wsr, H=H, I=I)
+        eaas.eaas_expert_ffn_grouped(dev["x"], r, dev["w_gate_up"], dev["w_down"], y, ws[:n], k,
+                                     dev["w_gate_up_scale"], dev["w_down_scale"])
+        eaas.eaas_unpermute_combine(y, r, dev["topk_weights"], out, E, I=I)
+        torch.cuda.synchronize()
+        assert torch.all(ws[n:] == 0xA5).item()
+        got = out.cpu().numpy()
+        assert np.array_equal(got.view(np.uint32), whole.view(np.uint32))
+        ref = O.expert_forward(d)["out"]
+        rms = float(np.sqrt((ref ** 2).mean()))
+        assert float(np.abs(got - ref).max()) <= TOL * rms
+    assert paths == ["few", "tiled" if wdtype == "bf16" else "few"]
